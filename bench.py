@@ -39,7 +39,7 @@ def kernel_source_hash():
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ("area.h", "kernels.hip", "kernels.h", "patop_internal.h"):
+    for f in ("area.h", "pairs.h", "kernels.hip", "kernels.h", "patop_internal.h"):
         with open(os.path.join(ROOT, "paper_2609_29253_amd", "csrc", f)) as fh:
             txt = fh.read()
         txt = re.sub(r"/\*.*?\*/", " ", txt, flags=re.S)

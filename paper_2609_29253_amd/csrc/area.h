@@ -9,23 +9,10 @@
 // nearest corner distance D_ac and farthest D_bd, Eq. closedform_rminrmax) and
 // hands each bin's area to a sink.
 //
-// Planar (Sec. 4.1): psi(u) = u^2 + x3^2, so in the plane of the rectangle the
-// shell is the annulus s0 <= u^2 + v^2 < s1 with s = r^2 - x3^2.  The area of
-// Eq. area_D_l_xi is evaluated in an equivalent form free of cancellation:
-//   2 |D^m| = int_{s0}^{s1} Theta(s) ds,
-// Theta(s) the angle subtended by the arc of radius sqrt(s) inside the
-// quadrant.  Theta = theta_hi - theta_lo, where theta_hi is acos(a/sqrt s) up to
-// the corner s_ad = a^2 + d^2 and asin(d/sqrt s) after it, theta_lo is
-// asin(c/sqrt s) up to s_bc and acos(b/sqrt s) after it.  Between these
-// breakpoints each term has the elementary antiderivative of Eq.
-// plane_primitive, rearranged as
-//   int_{s0}^{s1} acos(p/sqrt s) ds = (s1 - s0) acos(p/sqrt s1) + C,
-//   int_{s0}^{s1} asin(p/sqrt s) ds = (s1 - s0) asin(p/sqrt s1) - C,
-//   C = s0 (atan x - x) - x w0 dw,   w = sqrt(s - p^2), dw = w1 - w0,
-//   x = p dw / (p^2 + w0 w1)      (tan of the angle swept between s0 and s1),
-// so 2|D^m| = (s1 - s0) Theta(s1) + (corrections C), with Theta(s1) from one
-// atan2 of the chord between the two arc end points and every difference of
-// nearby squares taken from per-pair offsets that are exact to rounding.
+// Exact areas (planar, Sec. 4.1, and cylinder, Sec. 4.2): the closed form as the
+// difference of an elementary function between the bin's two edges (arc_sweep),
+// with the cylinder's curvature as a polynomial weight.  Elliptic integrals are
+// left to the quadrants whose weight the polynomials do not cover.
 //
 // Cylinder (Sec. 4.2): psi(u) = (R - rho)^2 + 4 R rho sin^2(u/2).  Alg. 4 is
 // followed literally (triples carried from edge to edge, Eq. area_D_l_xi,
@@ -158,319 +145,217 @@ __device__ __forceinline__ double sqrt64(double x)
 // compiler emits otherwise adds a denormal rescale and a correction step
 // (some 15 instructions)
 __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf(fmaxf(x, 0.0f)); }
-__device__ __forceinline__ double sqrt_t(double x) { return x > 0.0 ? x * rsq64(x) : 0.0; }
-// atan2 for y, x >= 0.  Small angles (y <= x/5) take the odd Taylor series of
-// atan(y/x), whose error is the rounding of a few correctly rounded operations;
-// the library routine's error, a smooth function of its argument, would be
-// shared by neighbouring voxels and survive their summation into one bin.
-__device__ __forceinline__ float atan2_t(float y, float x)
-{
-    if (y <= 0.2f * x) {
-        float t = y * __builtin_amdgcn_rcpf(x), u = t * t;
-        float p = fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.0f / 13, -1.0f / 11), 1.0f / 9), -1.0f / 7),
-                                       1.0f / 5), -1.0f / 3), 1.0f);
-        return t * p;
-    }
-    return atan2f(y, x);
-}
-__device__ __forceinline__ double atan2_t(double y, double x) { return atan2(y, x); }
-__device__ __forceinline__ float atan_t(float x) { return atanf(x); }
-__device__ __forceinline__ double atan_t(double x) { return atan(x); }
-
-// 1/x from the hardware reciprocal: v_rcp_f32 (1 ulp) in FP32, v_rcp_f64 with
-// two Newton steps in FP64
-__device__ __forceinline__ float rcp_t(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp_t(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-
-// atan(x) - x and atan(x) for x >= 0, the first without cancellation: halving
-//   atan x - x = 2 (atan y - y) - x^3 / (1 + sqrt(1 + x^2))^2,  y = x / (1 + sqrt(1 + x^2)),
-// (atan x = 2 atan y) then the Taylor series of atan y - y, through y^13; its
-// relative truncation error is ~0.2 y^12: below 1.2e-8 (FP32) from y < 0.25,
-// below 2e-13 (the FP64 series runs to y^23) from y < 0.1.  Above 4 the
-// library's atan gives both (there the difference has no cancellation).
-template <class T>
-struct AtanPair {
-    T mx;   // atan x - x
-    T a;    // atan x
-};
-
-template <class T> struct AtanMx;
-
-template <> struct AtanMx<float> {
-    static constexpr float kSmall = 0.25f;   // eval halves the angle from here on
-    // x < kSmall: the series alone, which is what eval computes there
-    static __device__ __forceinline__ AtanPair<float> small(float x)
-    {
-        float y = x * x;
-        float p = fmaf(y, fmaf(y, fmaf(y, fmaf(y, fmaf(y, -1.0f / 13, 1.0f / 11), -1.0f / 9), 1.0f / 7), -1.0f / 5),
-                       1.0f / 3);
-        const float t = -x * y * p;
-        return {t, x + t};
-    }
-    static __device__ __forceinline__ AtanPair<float> eval(float x)
-    {
-        if (x > 4.0f) {
-            const float a = atanf(x);
-            return {a - x, a};
-        }
-        const float x0 = x;
-        float acc = 0.0f, scale = 1.0f;
-        for (int i = 0; i < 4 && x >= 0.25f; ++i) {
-            float q = 1.0f + __builtin_amdgcn_sqrtf(fmaf(x, x, 1.0f));
-            float iq = __builtin_amdgcn_rcpf(q);
-            acc = fmaf(-scale * x * x * x, iq * iq, acc);
-            x *= iq;
-            scale *= 2.0f;
-        }
-        float y = x * x;
-        float p = fmaf(y, fmaf(y, fmaf(y, fmaf(y, fmaf(y, -1.0f / 13, 1.0f / 11), -1.0f / 9), 1.0f / 7), -1.0f / 5),
-                       1.0f / 3);
-        const float t = -scale * x * y * p;   // 2^k (atan y_k - y_k)
-        // after halvings the reduced argument carries their rounding (~10 ulp
-        // after four), harmless in atan x - x but not in the angle itself,
-        // which then comes from the library
-        return {acc + t, scale > 1.0f ? atanf(x0) : x + t};
-    }
-};
-
-template <> struct AtanMx<double> {
-    static constexpr double kSmall = 0.1;    // eval halves the angle from here on
-    // x < kSmall: the series alone, which is what eval computes there
-    static __device__ __forceinline__ AtanPair<double> small(double x)
-    {
-        double y = x * x;
-        double p = 1.0 / 23;
-        p = fma(y, p, -1.0 / 21);
-        p = fma(y, p, 1.0 / 19);
-        p = fma(y, p, -1.0 / 17);
-        p = fma(y, p, 1.0 / 15);
-        p = fma(y, p, -1.0 / 13);
-        p = fma(y, p, 1.0 / 11);
-        p = fma(y, p, -1.0 / 9);
-        p = fma(y, p, 1.0 / 7);
-        p = fma(y, p, -1.0 / 5);
-        p = fma(y, p, 1.0 / 3);
-        const double t = -x * y * p;
-        return {t, x + t};
-    }
-    static __device__ __forceinline__ AtanPair<double> eval(double x)
-    {
-        if (x > 4.0) {
-            const double a = atan(x);
-            return {a - x, a};
-        }
-        double acc = 0.0, scale = 1.0;
-        for (int i = 0; i < 4 && x >= 0.1; ++i) {
-            double q = 1.0 + sqrt64(fma(x, x, 1.0));
-            double iq = rcp64(q);
-            acc = fma(-scale * x * x * x, iq * iq, acc);
-            x *= iq;
-            scale *= 2.0;
-        }
-        double y = x * x;
-        double p = 1.0 / 23;
-        p = fma(y, p, -1.0 / 21);
-        p = fma(y, p, 1.0 / 19);
-        p = fma(y, p, -1.0 / 17);
-        p = fma(y, p, 1.0 / 15);
-        p = fma(y, p, -1.0 / 13);
-        p = fma(y, p, 1.0 / 11);
-        p = fma(y, p, -1.0 / 9);
-        p = fma(y, p, 1.0 / 7);
-        p = fma(y, p, -1.0 / 5);
-        p = fma(y, p, 1.0 / 3);
-        const double t = -scale * x * y * p;
-        return {acc + t, fma(scale, x, t)};
-    }
-};
 
 // ---------------------------------------------------------------------------
-// planar quadrant
+// areas as differences of a weighted area in a plane: planar quadrants, and
+// cylinder quadrants with the exact I_l
 // ---------------------------------------------------------------------------
+// With w = sqrt(mu) sin(u/2) the cylinder's level curve psi(u) + v^2 = r^2 is the
+// circle w^2 + v^2 = K, K = r^2 - (R - rho)^2, and with t = sqrt(mu) cos(u/2) the
+// hyperbola v^2 - t^2 = K, K = r^2 - (R + rho)^2; the surface element R du dv
+// becomes h dw dv with the weight h = 2 R / sqrt(mu (1 - x)), x = w^2 / mu
+// (resp. t^2 / mu).  h is smooth away from x = 1, so each quadrant takes it as a
+// polynomial p in om = S w^2 (S = +1 circle, -1 hyperbola), on the side of u =
+// pi/2 that keeps x away from 1, and the area nearer than r,
+//   int p(om) [clamp(y, c, d) - c] dw,   y = sqrt(K - om),
+// is elementary: with J_j = int om^j y dw,
+//   (2j + 2) J_j = (2j - 1) K J_{j-1} - w om^{j-1} y^3,   2 J_0 = w y + K Lambda,
+// Lambda = int dw / y the angle (or hyperbolic angle) the arc subtends.  An error
+// eps of p changes each area by at most eps of itself, whatever the cancellation
+// between edges, and costs no elliptic integral: two square roots, one inverse
+// function and about 6 N + 40 further FP64 operations per edge, with no loop
+// whose length differs between lanes.  A rectangle is the case h = 1, N = 0.
+//
+// End points of the arc: alpha starts clamped at the quadrant's near end N (u =
+// a) and moves along the line v = d once K passes the corner (N, d); beta moves
+// along v = c until the corner (F, c) and is then clamped at the far end F.
 
-// corners: 0 = (a, c), 1 = (a, d), 2 = (b, c), 3 = (b, d)
-template <class T>
-struct PlQuad {
-    T a, b, c, d, a2, c2;
-    T gu, gv, gx;          // b^2 - a^2, d^2 - c^2, gu - gv
-    T s[4];                // in-plane squared radius of each corner
-    T e[4], twoD[4];       // r_m - D_X = (m - j_X) + e_X;  2 D_X
-    T j[4];                // j_X, an integer (exact in T: |j_X| < 2^24)
-    int mfirst, mlast;     // bins touched
-    T two_r0m1;            // 2 r0 - 1: (r0 + m)^2 - (r0 + m - 1)^2 = two_r0m1 + 2m
+// h's factor (1 - x)^(-1/2) = (1 - xc)^(-1/2) (1 - tau)^(-1/2), tau = (x - xc) /
+// (1 - xc): interpolant of degree N at Chebyshev nodes on |tau| <= eta, relative
+// error 1.1e-10 (N = 5), 5.7e-11 (8), 6.2e-14 (7), 3.3e-13 (10)
+template <int N> struct Weight;
+template <> struct Weight<5> {
+    static constexpr double eta = 0.05;
+    static constexpr double c[] = {1.0000000001105098, 0.500000000102622, 0.3749992044251002, 0.3124992612121438,
+                                   0.274285523209855, 0.2468812331229099};
+};
+template <> struct Weight<8> {
+    static constexpr double eta = 0.16;
+    static constexpr double c[] = {1.0, 0.49999999704787307, 0.3749999971941834, 0.3125015348867947,
+                                   0.27343895879424956, 0.2458789227748675, 0.2253817687557605,
+                                   0.22053917177169305, 0.20689706937941357};
+};
+template <> struct Weight<7> {
+    static constexpr double eta = 0.05;
+    static constexpr double c[] = {0.9999999999999398, 0.49999999999994316, 0.37500000077050993,
+                                   0.31250000072773826, 0.27343595956342226, 0.24609229508034408,
+                                   0.2265708771687404, 0.21040290777839668};
+};
+template <> struct Weight<10> {
+    static constexpr double eta = 0.16;
+    static constexpr double c[] = {1.0, 0.5000000000212094, 0.3750000000203339, 0.31249998344974184,
+                                   0.2734374841330066, 0.2460973593854478, 0.2255893978103804, 0.20915235533051377,
+                                   0.19607355491324047, 0.1978170102153056, 0.1880321370533884};
 };
 
-// FP64 per-pair setup of one planar quadrant
-template <class T>
-__device__ __forceinline__ void pl_setup(PlQuad<T>& q, double a, double b, double c, double d,
-                                         double z2, double r0)
+// atan(k / 32) and log(1 + k / 32), k = 0..32: the work-group copies them to LDS
+// (kArcTab doubles), so that Lambda costs one division and a short series
+constexpr int kArcNodes = 33;
+constexpr int kArcTab = 2 * kArcNodes;
+static __device__ const double kArcTable[kArcTab] = {
+    0.0, 0.031239833430268277, 0.06241880999595735, 0.09347678115858947, 0.12435499454676144,
+    0.15499674192394097, 0.18534794999569476, 0.21535769969773805, 0.24497866312686414, 0.2741674511196588,
+    0.3028848683749714, 0.3310960767041321, 0.35877067027057225, 0.38588266939807375, 0.4124104415973873,
+    0.43833655985795783, 0.4636476090008061, 0.48833395105640554, 0.5123894603107377, 0.5358112379604637,
+    0.5585993153435624, 0.5807563535676704, 0.6022873461349642, 0.6231993299340659, 0.6435011087932844,
+    0.6632029927060933, 0.6823165548747481, 0.7008544078844502, 0.7188299996216245, 0.7362574289814281,
+    0.7531512809621944, 0.7695264804056583, 0.7853981633974483,
+    0.0, 0.030771658666753687, 0.06062462181643484, 0.08961215868968714, 0.11778303565638346,
+    0.1451820098444979, 0.17185025692665923, 0.19782574332991987, 0.22314355131420976, 0.24783616390458127,
+    0.27193371548364176, 0.2954642128938359, 0.3184537311185346, 0.3409265869705932, 0.3629054936893685,
+    0.38441169891033206, 0.4054651081081644, 0.4260843953109001, 0.44628710262841953, 0.46608972992459924,
+    0.4855078157817008, 0.5045560107523953, 0.5232481437645479, 0.5415972824327444, 0.5596157879354227,
+    0.5773153650348236, 0.5947071077466928, 0.6118015411059929, 0.6286086594223741, 0.6451379613735847,
+    0.661398482245365, 0.6773988235918061, 0.6931471805599453,
+};
+
+// X -+ X^3/3 + X^5/5 ... of a reduced argument |X| <= 1/64 (S = +1 atan, -1
+// atanh).  NW = 1: the terms after X in FP32 (<= 1.3e-6, so 8e-14 absolute)
+template <int S, int NW>
+__device__ __forceinline__ double arc_series(double X)
 {
-    q.a = T(a); q.b = T(b); q.c = T(c); q.d = T(d);
-    q.a2 = T(a * a); q.c2 = T(c * c);
-    double gu = (b - a) * (b + a), gv = (d - c) * (d + c);
-    q.gu = T(gu); q.gv = T(gv); q.gx = T(gu - gv);
-    const double uu[4] = {a, a, b, b}, vv[4] = {c, d, c, d};
+    if (NW == 1) {
+        const float xf = (float)X, u = xf * xf;
+        const float p = fmaf(u, 0.2f, S > 0 ? -1.0f / 3 : 1.0f / 3);
+        return X + (double)(xf * u * p);
+    }
+    const double u = X * X;
+    double p = fma(u, S > 0 ? -1.0 / 7 : 1.0 / 7, 1.0 / 5);
+    p = fma(u, p, S > 0 ? -1.0 / 3 : 1.0 / 3);
+    return fma(X * u, p, X);
+}
+
+// 1/x to the accuracy of the variant: one Newton step on the FP32 seed, or two
+// on the FP64 one
+template <int NW>
+__device__ __forceinline__ double rcp_nw(double x) { return NW >= 2 ? rcp64_full(x) : rcp64<1>(x); }
+
+// atan(num / den), num >= 0, den > 0, num <= den (beyond it only by rounding): the node k / 32 next to
+// the quotient, by its FP32 estimate, and the series at the tangent of the rest
+template <int NW>
+__device__ __forceinline__ double arc_atan(double num, double den, const double* tab)
+{
+    const float t = (float)num * __builtin_amdgcn_rcpf((float)den);
+    const float kf = rintf(fminf(fmaxf(t * 32.0f, 0.0f), 32.0f));
+    const double G = (double)(kf * (1.0f / 32));
+    const double X = fma(-G, den, num) * rcp_nw<NW>(fma(G, num, den));
+    return tab[(int)kf] + arc_series<1, NW>(X);
+}
+
+// log(a / b), a >= b > 0 (below it only by rounding): exponent and the leading
+// five bits of the quotient's FP32 estimate, then log of the rest = 2 atanh
+template <int NW>
+__device__ __forceinline__ double arc_log(double a, double b, const double* tab)
+{
+    const float qf = (float)a * __builtin_amdgcn_rcpf((float)b);
+    const int g = __float_as_int(qf);
+    const double G = (double)__int_as_float(g & 0x7ffc0000);
+    const int k = (g >> 18) & 31, e = ((g >> 23) & 255) - 127;
+    const double Gb = G * b;
+    const double X = (a - Gb) * rcp_nw<NW>(a + Gb);
+    return fma((double)e, 0.6931471805599453, fma(2.0, arc_series<-1, NW>(X), tab[kArcNodes + k]));
+}
+
+// one quadrant [N, F] x [c, d]: om and w of both ends, the squared distance of
+// the plane, and p's coefficients p_j as P = p_j / (2j + 2) and Q = p_j / (2j + 1)
+// times everything that multiplies the area
+template <int N>
+struct ArcQuad {
+    double base2, oN, wN, oF, wF, c, d, c2, d2;
+    double P[N + 1], Q[N + 1];
+    double S0, S1;          // the area function at the nearest and the farthest corner
+    int mfirst, mlast;      // bins touched
+};
+
+template <int N>
+__device__ __forceinline__ double horner(const double* q, double x)
+{
+    double a = q[N];
 #pragma unroll
-    for (int X = 0; X < 4; ++X) {
-        double s = uu[X] * uu[X] + vv[X] * vv[X];
-        double D = sqrt64(z2 + s);
-        double pos = D - r0;
-        double jj = floor(pos + 0.5);
-        q.j[X] = T(jj);
-        q.e[X] = T(jj - pos);
-        q.twoD[X] = T(2.0 * D);
-        q.s[X] = T(s);
-        if (X == 0) q.mfirst = (int)floor(pos) + 1;
-        if (X == 3) q.mlast = (int)ceil(pos);
-    }
-    q.two_r0m1 = T(2.0 * r0 - 1.0);
+    for (int j = N - 1; j >= 0; --j) a = fma(a, x, q[j]);
+    return a;
 }
 
-// s_m - s_X at the edge of bin m (given as T, an exact integer): the
-// difference m - j_X of two integers below 2^24 is exact in T
-template <class T>
-__device__ __forceinline__ T pl_qedge(const PlQuad<T>& q, int X, T m)
+// corners, the area function there and the bins; P and Q set
+template <int N, int S>
+__device__ __forceinline__ void arc_finish(ArcQuad<N>& q, double c, double d, double r0)
 {
-    T t = (m - q.j[X]) + q.e[X];
-    return t * (t + q.twoD[X]);
+    q.c = c; q.d = d; q.c2 = c * c; q.d2 = d * d;
+    q.S0 = q.wN * (d - c) * horner<N>(q.Q, q.oN);
+    q.S1 = q.wF * (d - c) * horner<N>(q.Q, q.oF);
+    q.mfirst = (int)floor(sqrt64(q.base2 + (q.oN + q.c2)) - r0) + 1;
+    q.mlast = (int)ceil(sqrt64(q.base2 + (q.oF + q.d2)) - r0);
 }
 
-// One arc end point moving along its line (at distance p from the origin, leg
-// w along the line) between in-plane squared radii s0 and s1 = s0 + dl:
-//   dw = w1 - w0 = dl / (w0 + w1),   x = tan(angle swept) = p dw / (p^2 + w0 w1),
-// and, with theta(s) = acos(p / sqrt s) for the end point's angle,
-//   int_{s0}^{s1} theta ds = dl theta(s1) + C,   C = s0 (atan x - x) - x w0 dw
-// (C for asin(p / sqrt s) with the opposite sign), while the angle swept is
-// atan x.  p = 0 or dl = 0 give C = 0 and no angle.
-template <class T>
-struct PlSwept {
-    T C, A;
-};
-
-template <class T>
-struct PlStep {
-    T x, dw;
-};
-
-template <class T>
-__device__ __forceinline__ PlStep<T> pl_step(T p, T dl, T w0, T w1)
+// The area function at radius r strictly between the nearest and the farthest
+// corner (its value at the corners is S0 and S1: it is the area nearer than r
+// plus S0)
+template <int N, int S, int NW>
+__device__ __forceinline__ double arc_edge(const ArcQuad<N>& q, double r, const double* tab)
 {
-    const T tiny = T(1e-30);
-    const T dw = dl * rcp_t(fmax(w0 + w1, tiny));
-    return {p * dw * rcp_t(fmax(fma(p, p, w0 * w1), tiny)), dw};
-}
-
-template <class T>
-__device__ __forceinline__ PlSwept<T> pl_swept(const PlStep<T>& st, T s0, T w0, const AtanPair<T>& at)
-{
-    return {fma(s0, at.mx, -st.x * w0 * st.dw), at.a};
-}
-
-// Walk the bins of a planar quadrant from its first one, mfirst, to
-// min(mlast, whi), handing those from wlo on to sink(m, area) (area in dr^2
-// units).  A bin is cut into pieces at the corners a^2 + d^2 (the upper end
-// point moves from the line u = a to v = d), b^2 + c^2 (the lower one from
-// v = c to u = b) and b^2 + d^2 (the end), at most three; each piece adds
-// dl Theta(s1) + (corrections of both end points) to twice the bin's area, and
-// Theta is carried from piece to piece by the angles the end points sweep (in
-// FP64), so no piece evaluates an inverse trigonometric function of its own.
-// The walk always starts at the first bin, also when the sink wants later ones
-// only (a later LDS pass, a later time tile): a walk started inside the range
-// would need Theta from one atan2 of the end points, accurate to FP32 rounding,
-// whose error then persists over the pair's remaining bins and leaves a step
-// in f.  The piece's kind of end and its squared-radius offsets are chosen by
-// selects, not branches.
-template <class T, class Sink>
-__device__ __forceinline__ void pl_sweep(const PlQuad<T>& q, int wlo, int whi, T wgt, Sink& sink)
-{
-    const int mb = q.mfirst, me = min(q.mlast, whi);
-    if (mb > me || q.mlast < wlo) return;
-    // state at the start of the piece: offsets Q0[X] = s0 - s_X (X = AD, BC, BD),
-    // s0, the kind of start, which lines the end points are on, their legs, Theta
-    T Q01 = -q.gv, Q02 = -q.gu, Q03 = -(q.gu + q.gv);
-    T s0 = q.s[0], wh0 = q.c, wl0 = q.a;
-    bool k0e = false, k0a = false, k0b = false;   // the piece starts at a bin edge, at corner (a, d),
-                                                  // at (b, c); else at (a, c)
-    bool hiS = false, loA = false;
-    // Theta just above the nearest corner (a, c): 0, unless the corner is the
-    // origin (the voxel's projection), where the arc is a quarter circle
-    double th = (q.a > T(0) || q.c > T(0)) ? 0.0 : 0.5 * M_PI;
-    int m = mb;
-    T acc = T(0);
-    for (int guard = 0; guard < 1 << 20; ++guard) {
-        const T fm = T(m);
-        T Qe[4];
+    const double K = fma(r, r, -q.base2);
+    const double od = K - q.d2, oc = K - q.c2;
+    const bool onD = od > q.oN, onC = oc < q.oF;
+    const double oa = fmax(od, q.oN), ob = fmin(oc, q.oF);
+    const double ra = sqrt64<NW>(onD ? (S > 0 ? od : -od) : K - q.oN);
+    const double rb = sqrt64<NW>(onC ? (S > 0 ? oc : -oc) : K - q.oF);
+    const double wa = onD ? ra : q.wN, ya = onD ? q.d : ra;
+    const double wb = onC ? rb : q.wF, yb = onC ? q.c : rb;
+    double lam;   // Lambda
+    if (S > 0)    // twice the half angle, so that the denominator stays positive
+        lam = 2.0 * arc_atan<NW>(fma(wb, ya, -wa * yb), K + fma(wa, wb, ya * yb), tab);
+    else
+        lam = -arc_log<NW>(wa + ya, wb + yb, tab);
+    if constexpr (N == 0) {
+        const double Ba = wa * fma(ya, q.P[0], -q.d * q.Q[0]);
+        return fma(q.P[0] * K, lam, fma(wb, fma(yb, q.P[0], -q.c * q.Q[0]), -Ba));
+    } else {
+        // (2j + 2) D[j] = p_j + (2j + 1) K D[j + 1]: the sum of p_j J_j is
+        // D[0] (w y + K Lambda) - w y^3 (D[1] + D[2] om + ...)
+        double D[N + 1];
+        D[N] = q.P[N];
 #pragma unroll
-        for (int X = 0; X < 4; ++X) Qe[X] = pl_qedge(q, X, fm);
-        const T dlE = fma(T(2), fm, q.two_r0m1);   // from edge to edge: (r0 + m)^2 - (r0 + m - 1)^2
-        // the piece ends at the next corner inside the bin, else at its outer
-        // edge; every choice below is a chain of selects between values that
-        // are all computed (the common case has no divergent branch)
-        const bool cad = !hiS && Qe[1] > T(0), cbc = !loA && Qe[2] > T(0);
-        const bool atAD = cad && (!cbc || q.gx >= T(0));
-        const bool atBC = cbc && !atAD;
-        const bool atBD = !cad && !cbc && Qe[3] > T(0);
-        const bool edge = !cad && !cbc && !atBD;
-        // Q1[X] = s1 - s_X: at a corner Y it is s_Y - s_X
-        T Q10 = q.gu + q.gv, Q11 = q.gu, Q12 = q.gv, Q13 = T(0);   // at (b, d)
-        Q10 = atBC ? q.gu : Q10; Q11 = atBC ? q.gx : Q11; Q12 = atBC ? T(0) : Q12; Q13 = atBC ? -q.gv : Q13;
-        Q10 = atAD ? q.gv : Q10; Q11 = atAD ? T(0) : Q11; Q12 = atAD ? -q.gx : Q12; Q13 = atAD ? -q.gu : Q13;
-        Q10 = edge ? Qe[0] : Q10; Q11 = edge ? Qe[1] : Q11; Q12 = edge ? Qe[2] : Q12; Q13 = edge ? Qe[3] : Q13;
-        // s1 - s0 from the quantity that is exactly zero at one end
-        T dlc = k0a ? Q11 : Q10;   // from a corner: its offset at s1
-        dlc = k0b ? Q12 : dlc;
-        T dle = atBC ? -Q02 : -Q03;   // from an edge: the corner's offset at s0, or a whole bin
-        dle = atAD ? -Q01 : dle;
-        dle = edge ? dlE : dle;
-        const T dl = k0e ? dle : dlc;
-        // legs of the end points at s1 on their current lines
-        const T wh1 = sqrt_t(hiS ? Q11 + q.a2 : Q10 + q.c2);
-        const T wl1 = sqrt_t(loA ? Q12 + q.c2 : Q10 + q.a2);
-        const PlStep<T> sH = pl_step(hiS ? q.d : q.a, dl, wh0, wh1);
-        const PlStep<T> sL = pl_step(loA ? q.b : q.c, dl, wl0, wl1);
-        // atan x - x and atan x of both steps: the short series unless some
-        // lane of the wave needs the angle halvings (rare: ~1 % of the pieces
-        // on 50 mm geometries), decided once per wave so that the common case
-        // has no divergent branch; both give the same result below kSmall
-        AtanPair<T> aH, aL;
-        if (__any(fmax(sH.x, sL.x) >= AtanMx<T>::kSmall)) {
-            aH = AtanMx<T>::eval(sH.x);
-            aL = AtanMx<T>::eval(sL.x);
-        } else {
-            aH = AtanMx<T>::small(sH.x);
-            aL = AtanMx<T>::small(sL.x);
-        }
-        const PlSwept<T> H = pl_swept(sH, s0, wh0, aH);
-        const PlSwept<T> Lo = pl_swept(sL, s0, wl0, aL);
-        const T sh = hiS ? T(-1) : T(1), sl = loA ? T(-1) : T(1);
-        th += (double)fma(sh, H.A, sl * Lo.A);
-        acc += fma(dl, (T)th, fma(sh, H.C, sl * Lo.C));
-        // advance
-        Q01 = Q11; Q02 = Q12; Q03 = Q13;
-        s0 = Q10 + q.s[0];
-        k0e = edge;
-        k0a = atAD;
-        k0b = atBC;
-        wh0 = atAD ? q.a : wh1;
-        wl0 = atBC ? q.c : wl1;
-        hiS = hiS || atAD;
-        loA = loA || atBC;
-        if (edge || atBD) {
-            if (m >= wlo) sink(m, T(0.5) * wgt * acc);
-            acc = T(0);
-            if (atBD || m >= me) break;
-            ++m;
-        }
+        for (int j = N; j > 0; --j) D[j - 1] = fma(K * ((2.0 * j - 1.0) / (2.0 * j)), D[j], q.P[j - 1]);
+        const double Ba = wa * fma(ya, fma(-ya * ya, horner<N - 1>(D + 1, oa), D[0]), -q.d * horner<N>(q.Q, oa));
+        const double Bb = wb * fma(yb, fma(-yb * yb, horner<N - 1>(D + 1, ob), D[0]), -q.c * horner<N>(q.Q, ob));
+        return fma(D[0] * K, lam, Bb - Ba);
     }
+}
+
+// hand the bins wlo .. whi of the quadrant to sink(m, area).  Every edge is
+// evaluated on its own, so a walk that the window clips starts there, with the
+// same areas; the first and the last edge of the quadrant lie outside its
+// corners and are set (S0, S1), which also makes every lane's loop one edge shorter
+template <int N, int S, int NW, class Sink>
+__device__ __forceinline__ void arc_sweep(const ArcQuad<N>& q, double r0, int wlo, int whi, const double* tab,
+                                          Sink& sink)
+{
+    const int mb = max(q.mfirst, wlo), me = min(q.mlast, whi);
+    if (mb > me) return;
+    const bool tail = me == q.mlast;
+    const int mend = tail ? me - 1 : me;   // the last edge evaluated
+    double s0 = q.S0;
+    for (int m = mb > q.mfirst ? mb - 1 : mb; m <= mend; ++m) {
+        const double s1 = arc_edge<N, S, NW>(q, r0 + m, tab);
+        if (m >= mb) sink(m, s1 - s0);
+        s0 = s1;
+    }
+    if (tail) sink(me, q.S1 - s0);
 }
 
 // ---------------------------------------------------------------------------
-// cylinder quadrant (FP64)
+// cylinder quadrant by its arc integrals I_l (FP64): the trapezoidal and the
+// tabulated I_l, and the exact one where arc_sweep does not serve
 // ---------------------------------------------------------------------------
 
 struct CyPair {

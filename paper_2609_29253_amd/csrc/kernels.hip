@@ -34,6 +34,7 @@
 
 #include "area.h"
 #include "kernels.h"
+#include "pairs.h"
 
 namespace patop {
 
@@ -181,235 +182,12 @@ __device__ __forceinline__ void frame_coords(const TrDev& T, int ix, int iy, int
     for (int a = 0; a < 3; ++a) x[a] = fma(T.g[a][0], ix, fma(T.g[a][1], iy, fma(T.g[a][2], iz, T.base[a])));
 }
 
-// ---------------------------------------------------------------------------
-// per-pair geometry: reflected quadrants of the parameter rectangle
-// (Eq. uvminmax; Eq. folded_intervals for the cylinder), built one at a time
-// ---------------------------------------------------------------------------
-
-// Two reflected intervals that share an end point, [e, p] and [e, q] (or [p, e]
-// and [q, e]), cover the same parameter region as the interval between e and
-// the nearer of p, q counted twice plus the remainder counted once.  Sweeping
-// the merged form visits each bin of the shared part once instead of twice.
-struct WInt {
-    double lo[2], hi[2];
-    float w[2];
-    int n;
-};
-
-// intervals [0, A] and [0, B] (A, B >= 0), Eq. uvminmax with the origin inside.
-// MERGE: the shared-part form above; else the two intervals as they are, which
-// an approximation that is not additive over sub-intervals (the trapezoidal
-// I_l: the chord of a split arc is not the chord of the arc) must use.
-template <bool MERGE = true>
-__device__ __forceinline__ void split_at_zero(double A, double B, WInt& I)
+// the work-group's copy of kArcTable (no barrier here)
+template <int STRIDE>
+__device__ __forceinline__ void load_arc_table(double* tab)
 {
-    if (MERGE) {
-        double m = fmin(A, B), M = fmax(A, B);
-        I.lo[0] = 0.0; I.hi[0] = m; I.w[0] = 2.0f;
-        I.lo[1] = m;   I.hi[1] = M; I.w[1] = 1.0f;
-    } else {
-        I.lo[0] = 0.0; I.hi[0] = A; I.w[0] = 1.0f;
-        I.lo[1] = 0.0; I.hi[1] = B; I.w[1] = 1.0f;
-    }
-    I.n = 2;
+    for (int i = threadIdx.x; i < kArcTab; i += STRIDE) tab[i] = kArcTable[i];
 }
-
-// the reflected intervals of [lo, hi] about 0 (Eq. uvminmax)
-template <bool MERGE = true>
-__device__ __forceinline__ void fold_line(double lo, double hi, WInt& I)
-{
-    if (lo < 0.0 && 0.0 < hi) { split_at_zero<MERGE>(-lo, hi, I); return; }
-    double a = fabs(lo), b = fabs(hi);
-    I.lo[0] = fmin(a, b); I.hi[0] = fmax(a, b); I.w[0] = 1.0f;
-    I.lo[1] = I.hi[1] = 0.0; I.w[1] = 0.0f;
-    I.n = 1;
-}
-
-template <class AT>
-struct PlanarPair {
-    WInt U, V;
-    double z2;
-    __device__ __forceinline__ void bind(double*, const double2*) {}
-    __device__ __forceinline__ void setup(const TrDev& T, const double x[3], double)
-    {
-        double L1 = T.p[0], L2 = T.p[1];
-        fold_line(-L1 - x[0], L1 - x[0], U);
-        fold_line(-L2 - x[1], L2 - x[1], V);
-        z2 = x[2] * x[2];
-    }
-    // bins wlo .. whi of each quadrant reach the sink (each quadrant is walked
-    // from its first bin, see pl_sweep)
-    template <class Sink>
-    __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
-    {
-        // the lane's non-empty quadrants first, so lanes step through their k-th
-        // quadrant together
-        int list = 0, nq = 0;
-#pragma unroll
-        for (int qi = 0; qi < 4; ++qi) {
-            const int i = qi >> 1, j = qi & 1;
-            const bool ok = i < U.n && j < V.n && (i ? U.hi[1] > U.lo[1] : U.hi[0] > U.lo[0]) &&
-                            (j ? V.hi[1] > V.lo[1] : V.hi[0] > V.lo[0]);
-            if (ok) { list |= qi << (2 * nq); ++nq; }
-        }
-#pragma unroll 1
-        for (int t = 0; t < nq; ++t) {
-            const int qi = (list >> (2 * t)) & 3;
-            const int i = qi >> 1, j = qi & 1;
-            const double a = i ? U.lo[1] : U.lo[0], b = i ? U.hi[1] : U.hi[0];
-            const double c = j ? V.lo[1] : V.lo[0], d = j ? V.hi[1] : V.hi[0];
-            const float w = (i ? U.w[1] : U.w[0]) * (j ? V.w[1] : V.w[0]);
-            PlQuad<AT> q;
-            pl_setup(q, a, b, c, d, z2, r0);
-            pl_sweep(q, wlo, whi, (AT)w, sink);
-        }
-    }
-};
-
-__device__ __forceinline__ double wrap_pi(double u)
-{
-    if (u <= -M_PI) u += 2.0 * M_PI;
-    if (u <= -M_PI) u += 2.0 * M_PI;
-    if (u > M_PI) u -= 2.0 * M_PI;
-    if (u > M_PI) u -= 2.0 * M_PI;
-    return u;
-}
-
-// The interval ends of the folded quadrants live in LDS (one column per thread,
-// kBoxSlots doubles), read back per quadrant: kept in registers they would be
-// live through every sweep and pushed to scratch memory at three or four waves
-// per SIMD.
-constexpr int kBoxSlots = 8;
-
-// MERGE of the folded intervals holds for every I_l that is a difference of a
-// function of the end points (exact, tables); not for the chord.
-template <int NW, int IL, int STRIDE = kThreads>   // STRIDE: threads of the work-group (the table's row)
-struct CylinderPair {
-    static constexpr bool kMerge = IL != kIlTrapezoid;
-    CyPair P;
-    double* box;             // this thread's column of the LDS box table
-    int list, nq;            // non-empty quadrants (2 bits each, in sweep order) and their number
-    int wbits;               // quadrant weights: bits 0/1 the U intervals, 2/3 the V intervals (set = 2)
-    __device__ __forceinline__ void bind(double* table, const double2* lut)
-    {
-        box = table + threadIdx.x;
-        P.lut = lut;
-    }
-    __device__ __forceinline__ void setup(const TrDev& T, const double x[3], double)
-    {
-        WInt U, V;
-        double R = T.p[0], th = T.p[1], Lz = T.p[2];
-        // a voxel on the focal line (rho = 0, Sec. 4.2) has no angular position;
-        // rounding of its frame coordinates leaves rho at ~1e-16 of them, which
-        // is snapped to 0 so that its angle is 0 rather than an arbitrary one
-        double rho = sqrt64(x[0] * x[0] + x[1] * x[1]);
-        if (rho <= 1e-10 * R) rho = 0.0;
-        double thi = (rho > 0.0) ? atan2_full(x[1], x[0]) : 0.0;
-        P.R = R;
-        P.dm = fabs(R - rho);
-        P.mu = 4.0 * R * rho;
-        P.imu = P.mu > 0.0 ? rcp64_full(P.mu) : 0.0;
-        double u1 = wrap_pi(-th - thi), u2 = wrap_pi(th - thi);
-        // Eq. folded_intervals (merged where the areas are exact, see split_at_zero)
-        if (u1 < 0.0 && 0.0 < u2) {
-            split_at_zero<kMerge>(-u1, u2, U);
-        } else if (u2 < u1) {
-            // [u1, pi] and [-u2, pi]
-            if (!kMerge) {
-                U.lo[0] = u1;  U.hi[0] = M_PI; U.w[0] = 1.0f;
-                U.lo[1] = -u2; U.hi[1] = M_PI; U.w[1] = 1.0f;
-            } else {
-                double m = fmax(u1, -u2), M = fmin(u1, -u2);
-                U.lo[0] = m; U.hi[0] = M_PI; U.w[0] = 2.0f;
-                U.lo[1] = M; U.hi[1] = m;    U.w[1] = 1.0f;
-            }
-            U.n = 2;
-        } else if (0.0 <= u1) {
-            U.lo[0] = u1; U.hi[0] = u2; U.w[0] = 1.0f; U.n = 1;
-        } else {
-            U.lo[0] = -u2; U.hi[0] = -u1; U.w[0] = 1.0f; U.n = 1;
-        }
-        fold_line<kMerge>(-Lz - x[2], Lz - x[2], V);
-        // the non-empty quadrants in decreasing order of their number of bins
-        // (nearest to farthest corner, estimated in FP32): the wave steps
-        // through every lane's t-th quadrant together, so the lanes' longest
-        // sweeps share one trip count
-        bool ok[4];
-        float len[4];
-        {
-            const float muf = (float)P.mu, dm2 = (float)(P.dm * P.dm);
-            float pa[2], pb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float sa = __sinf(0.5f * (float)(i < U.n ? U.lo[i] : 0.0));
-                const float sb = __sinf(0.5f * (float)(i < U.n ? U.hi[i] : 0.0));
-                pa[i] = fmaf(muf * sa, sa, dm2);
-                pb[i] = fmaf(muf * sb, sb, dm2);
-            }
-#pragma unroll
-            for (int qi = 0; qi < 4; ++qi) {
-                const int i = qi >> 1, j = qi & 1;
-                ok[qi] = i < U.n && j < V.n && (i ? U.hi[1] > U.lo[1] : U.hi[0] > U.lo[0]) &&
-                         (j ? V.hi[1] > V.lo[1] : V.hi[0] > V.lo[0]);
-                const float c = (float)(j < V.n ? V.lo[j] : 0.0), d = (float)(j < V.n ? V.hi[j] : 0.0);
-                len[qi] = ok[qi] ? fmaxf(sqrt_t(fmaf(d, d, pb[i])) - sqrt_t(fmaf(c, c, pa[i])), 0.0f) : -1.0f;
-            }
-        }
-        list = 0;
-        nq = 0;
-#pragma unroll
-        for (int qi = 0; qi < 4; ++qi) {
-            int rank = 0;
-#pragma unroll
-            for (int qj = 0; qj < 4; ++qj)
-                rank += (qj != qi) && (len[qj] > len[qi] || (len[qj] == len[qi] && qj < qi));
-            if (ok[qi]) { list |= qi << (2 * rank); ++nq; }
-        }
-        wbits = (U.w[0] > 1.5f ? 1 : 0) | (U.w[1] > 1.5f ? 2 : 0) | (V.w[0] > 1.5f ? 4 : 0) |
-                (V.w[1] > 1.5f ? 8 : 0);
-        box[0 * STRIDE] = U.lo[0]; box[1 * STRIDE] = U.hi[0];
-        box[2 * STRIDE] = U.lo[1]; box[3 * STRIDE] = U.hi[1];
-        box[4 * STRIDE] = V.lo[0]; box[5 * STRIDE] = V.hi[0];
-        box[6 * STRIDE] = V.lo[1]; box[7 * STRIDE] = V.hi[1];
-    }
-    __device__ __forceinline__ void quadrant(int qi, double& a, double& b, double& c, double& d, double& w) const
-    {
-        const int i = qi >> 1, j = qi & 1;
-        a = box[(2 * i) * STRIDE]; b = box[(2 * i + 1) * STRIDE];
-        c = box[(4 + 2 * j) * STRIDE]; d = box[(5 + 2 * j) * STRIDE];
-        w = (double)((1 + ((wbits >> i) & 1)) * (1 + ((wbits >> (2 + j)) & 1)));
-    }
-    // bins wlo .. whi of each quadrant reach the sink; each edge is evaluated
-    // on its own, so the walk starts at max(mfirst, wlo)
-    template <class Sink>
-    __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
-    {
-#pragma unroll 1
-        for (int t = 0; t < nq; ++t) {
-            double a, b, c, d, w;
-            quadrant((list >> (2 * t)) & 3, a, b, c, d, w);
-            CyQuad q;
-            cy_setup(q, P, a, b, c, d, r0);
-            cy_sweep<NW, IL>(q, P, r0, wlo, whi, w, sink);
-        }
-    }
-};
-
-// Cylinder areas are FP64 in both variants.  With FP32 input and output one
-// correction step after the FP32 seeds of the square roots and reciprocals
-// (2^-46 after it) is enough; the FP64 variant takes two after the FP64 ones.
-template <class Real> struct CylNewton { static constexpr int value = 2; };
-template <> struct CylNewton<float> { static constexpr int value = 1; };
-
-// IL: how the cylinder's I_l is evaluated (kIlExact, kIlTrapezoid, kIlTable);
-// the planar I_l is exact either way
-template <int SHAPE, class AT, class Real, int IL, int STRIDE = kThreads> struct PairOf;
-template <class AT, class Real, int IL, int STRIDE> struct PairOf<0, AT, Real, IL, STRIDE> {
-    using type = PlanarPair<AT>;
-};
-template <class AT, class Real, int IL, int STRIDE> struct PairOf<1, AT, Real, IL, STRIDE> {
-    using type = CylinderPair<CylNewton<Real>::value, IL, STRIDE>;
-};
 
 // ---------------------------------------------------------------------------
 // forward, closed-form areas
@@ -422,17 +200,14 @@ constexpr int kSparseGrid = 4096;
 
 // Waves per SIMD the closed-form kernels are built for (one-wave work-groups in
 // the dense and sparse forward and the adjoint, 256-thread ones in the time
-// tiles).  Cylinders for one or two volumes: four, in 128 VGPRs with a few
-// spills outside the sweep; with more volumes the spills grow (120-210 bytes
-// per lane) and they keep three.  The planar sweep in FP64 for four or eight
-// volumes spills 300 bytes per lane at three and runs faster at two (1.75x for
-// the adjoint of eight volumes); for one volume three is faster despite its
-// spills (9 %).  The FP32 planar kernels fit four waves without spills
-// (112-125 VGPRs).
+// tiles).  The planar kernels hold 107-127 VGPRs without spills and run at four,
+// except FP64 with eight volumes (142).  Cylinders for one or two volumes: four,
+// in 128 VGPRs with spills outside the loops over edges; with more volumes the
+// spills grow and they keep three.
 template <int SHAPE, class AT, int NB>
 constexpr int closed_waves()
 {
-    return SHAPE == 1 ? (NB <= 2 ? 4 : 3) : (sizeof(AT) == 8 ? (NB >= 4 ? 2 : 3) : (NB <= 2 ? 4 : 3));
+    return SHAPE == 1 ? (NB <= 2 ? 4 : 3) : (sizeof(AT) == 8 && NB == 8 ? 3 : 4);
 }
 
 // ---------------------------------------------------------------------------
@@ -440,6 +215,14 @@ constexpr int closed_waves()
 // ---------------------------------------------------------------------------
 
 constexpr int kWave = 64;          // threads of a one-wave work-group: a 4 x 4 x 4 voxel cube
+
+// orders a one-wave work-group's LDS operations before it against those after
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // LDS window of a one-wave work-group, in bytes, shared by its volumes: with
 // sixteen of them per CU (four waves per SIMD) each may hold 10 KB; the
@@ -458,7 +241,7 @@ constexpr int wave_window_bytes()
 template <int SHAPE, class AT, int NB, class Real, int IL>
 __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy, int iz, bool valid, int64_t idx,
                                                 int kbeg, int kend, const Real* __restrict__ coef,
-                                                double* __restrict__ f, double* hist, double* box)
+                                                double* __restrict__ f, double* hist, double* box, const double* tab)
 {
     constexpr int HE = wave_window_bytes<SHAPE>() / (int)sizeof(double);
     constexpr int HW = HE / NB;          // shells per pass
@@ -476,8 +259,8 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
     for (int kk = kbeg; kk < kend; ++kk) {
         const int k = P.kperm[kk];
         int wlo, whi;
-        typename PairOf<SHAPE, AT, Real, IL, kWave>::type pair;
-        pair.bind(box, P.lut);
+        typename PairOf<SHAPE, Real, IL, kWave>::type pair;
+        pair.bind(box, P.lut, tab);
         {
             const TrDev T = P.tr[k];
             double x[3];
@@ -493,9 +276,7 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
             for (int i = l; i < wn; i += kWave)
 #pragma unroll
                 for (int b = 0; b < NB; ++b) hist[b * HW + i] = 0.0;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_lds_order();
             if (nz) {
                 auto sink = [&](int m, auto area) {
 #pragma unroll
@@ -503,9 +284,7 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
                 };
                 pair.sweep(plo, phi, sink, P.r0);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_lds_order();
             for (int i = l; i < wn * S; i += kWave) {
                 const int jj = i / S;
                 const int64_t m = (int64_t)(plo + jj - 1) * S + 1 + (i - jj * S);
@@ -516,9 +295,7 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
                     if (v != 0.0) unsafeAtomicAdd(&f[((int64_t)b * P.K + k) * P.Mcount + (m - P.Mlo)], v * S);
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_lds_order();
         }
     }
 }
@@ -532,6 +309,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
 {
     __shared__ double hist[wave_window_bytes<SHAPE>() / sizeof(double)];   // [NB][shells per pass]
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
+    __shared__ double tab[kArcTab];
     const int ncx = (int)((P.n[0] + 3) / 4), ncy = (int)((P.n[1] + 3) / 4);
     const int cid = blockIdx.x;
     const int x0 = (cid % ncx) * 4, y0 = ((cid / ncx) % ncy) * 4, z0 = (cid / (ncx * ncy)) * 4;
@@ -540,8 +318,10 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
     const bool valid = ix < P.n[0] && iy < P.n[1] && iz < P.n[2];
     const int64_t idx = valid ? ix + P.n[0] * (iy + P.n[1] * (int64_t)iz) : 0;
     const int kbeg = blockIdx.y * P.kchunk;
+    load_arc_table<kWave>(tab);
+    wave_lds_order();
     fwd_wave_voxels<SHAPE, AT, NB, Real, IL>(P, ix, iy, iz, valid, idx, kbeg, min(P.nk, kbeg + P.kchunk), coef, f,
-                                             hist, box);
+                                             hist, box, tab);
 }
 
 // Sparse forward: work items (64 consecutive entries of the support list, a
@@ -556,6 +336,9 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
 {
     __shared__ double hist[wave_window_bytes<SHAPE>() / sizeof(double)];   // [NB][shells per pass]
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
+    __shared__ double tab[kArcTab];
+    load_arc_table<kWave>(tab);
+    wave_lds_order();
     const int64_t total = *P.sup_total;
     const int64_t nchunks = (P.nk + P.kchunk - 1) / P.kchunk;
     const int64_t items = (total + kWave - 1) / kWave * nchunks;
@@ -567,7 +350,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
         const int ix = (int)(idx % P.n[0]), iy = (int)((idx / P.n[0]) % P.n[1]), iz = (int)(idx / (P.n[0] * P.n[1]));
         const int kbeg = (int)(it % nchunks) * P.kchunk;
         fwd_wave_voxels<SHAPE, AT, NB, Real, IL>(P, ix, iy, iz, valid, idx, kbeg, min(P.nk, kbeg + P.kchunk), coef,
-                                                 f, hist, box);
+                                                 f, hist, box, tab);
     }
 }
 
@@ -589,6 +372,7 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
 {
     extern __shared__ double hist[];   // [NB][tile]
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kThreads : 1];
+    __shared__ double tab[kArcTab];
     __shared__ int cand[kThreads];
     __shared__ int ncand;
     const int item = items[blockIdx.x];
@@ -597,6 +381,7 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
     const int tlo = (int)P.Jlo + t * tile;
     const int thi = min((int)P.Jhi, tlo + tile - 1);
     for (int i = threadIdx.x; i < NB * tile; i += kThreads) hist[i] = 0.0;
+    load_arc_table<kThreads>(tab);   // ordered by the barriers before the first sweep
     for (int c0 = 0; c0 < nbricks; c0 += kThreads) {
         const int b = c0 + threadIdx.x;
         bool hit = false;
@@ -624,8 +409,8 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
                 nz |= p0[v] != 0.0;
             }
             if (!__syncthreads_or(nz)) continue;
-            typename PairOf<SHAPE, AT, Real, IL>::type pair;
-            pair.bind(box, P.lut);
+            typename PairOf<SHAPE, Real, IL>::type pair;
+            pair.bind(box, P.lut, tab);
             {
                 const TrDev T = P.tr[k];
                 double x[3];
@@ -637,10 +422,10 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
 #pragma unroll
                     for (int v = 0; v < NB; ++v) atomicAdd(&hist[v * tile + (m - tlo)], p0[v] * (double)area);
                 };
-                // planar quadrants are walked from their first bin whatever
-                // the tile, and a cylinder walk evaluates each edge on its own
-                // (the edges outside its quadrant set as in the cube forward):
-                // the areas are the cube forward's bit for bit
+                // every edge is evaluated on its own (those outside a quadrant
+                // are set, as in the cube forward), so a tile's areas are the
+                // cube forward's; a cylinder wave's choice between the degrees
+                // of the weight differs by the polynomials' error only
                 pair.sweep(tlo, thi, sink, P.r0);
             }
         }
@@ -700,6 +485,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
     __shared__ Real Ws[HE];              // [NB][HB]
     constexpr int HB = HE / NB;          // shells per pass
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
+    __shared__ double tab[kArcTab];
     const int ncx = (int)((P.n[0] + 3) / 4), ncy = (int)((P.n[1] + 3) / 4);
     const int cid = blockIdx.x;
     const int x0 = (cid % ncx) * 4, y0 = ((cid / ncx) % ncy) * 4, z0 = (cid / (ncx * ncy)) * 4;
@@ -710,14 +496,16 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
     double acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = 0.0;
+    load_arc_table<kWave>(tab);
+    wave_lds_order();
     const int kbeg = blockIdx.y * P.kchunk, kend = min(P.nk, kbeg + P.kchunk);
     const int S = P.step;
     const int64_t Mhi = P.Mlo + P.Mcount - 1;
     for (int kk = kbeg; kk < kend; ++kk) {
         const int k = P.kperm[kk];
         int wlo, whi;
-        typename PairOf<SHAPE, AT, Real, IL, kWave>::type pair;
-        pair.bind(box, P.lut);
+        typename PairOf<SHAPE, Real, IL, kWave>::type pair;
+        pair.bind(box, P.lut, tab);
         {
             const TrDev T = P.tr[k];
             double x[3];
@@ -730,9 +518,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
         for (int plo = wlo; plo <= whi; plo += HB) {
             const int phi = min(whi, plo + HB - 1);
             const int wn = phi - plo + 1;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_lds_order();
             // transpose of the even split: each shell gathers its fine bins (Remark 1)
             for (int i = l; i < wn; i += kWave)
 #pragma unroll
@@ -745,9 +531,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
                     }
                     Ws[b * HB + i] = (Real)(a * S);
                 }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            wave_lds_order();
             if (valid) {
                 AT part[NB];
 #pragma unroll
@@ -930,6 +714,8 @@ __global__ __launch_bounds__(kThreads) void k_count(KParams P, int quad, unsigne
 {
     __shared__ unsigned long long red[2];
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kThreads : 1];
+    __shared__ double tab[kArcTab];
+    load_arc_table<kThreads>(tab);
     if (threadIdx.x < 2) red[threadIdx.x] = 0;
     __syncthreads();
     Brick Bk;
@@ -944,8 +730,8 @@ __global__ __launch_bounds__(kThreads) void k_count(KParams P, int quad, unsigne
             const int lo = (int)P.Jlo, hi = (int)P.Jhi;
             int nb = 0;
             auto sink = [&](int, auto) { ++nb; };
-            typename PairOf<SHAPE, double, double, kIlExact>::type pair;
-            pair.bind(box, nullptr);
+            typename PairOf<SHAPE, double, kIlExact>::type pair;
+            pair.bind(box, nullptr, tab);
             pair.setup(T, x, P.r0);
             pair.sweep(lo, hi, sink, P.r0);
             evals += nb;

@@ -1,0 +1,169 @@
+"""The kernels' exact shell areas on the CPU: the pair sweeps of area.h and
+pairs.h, compiled for the host, bin by bin against the same areas in 30 digits.
+
+Reference: the area of the surface nearer than r, from signed quadrants anchored
+at the voxel's projection (rectangle) or angle (cylinder, incomplete elliptic
+integrals of the second kind), and its differences between bin edges.
+
+Tolerance, of the pair's largest area: the kernels difference an area function
+whose terms reach `size` = (K + |w y|) x weight at the pair's corners, each with
+a few roundings of the variant (2^-52 with two Newton steps, 1.5 x 2^-45 with one),
+64 in all, plus the weight polynomial's relative error and the reference's own
+rounding of its inputs; where Carlson's integral serves, its stated error (5e-10
+and 1e-13 of an edge)."""
+import ctypes
+import math
+import os
+import shutil
+import subprocess
+
+import mpmath as mp
+import numpy as np
+import pytest
+
+from conftest import ROOT
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+
+UNIT = {0: 1.5 * 2.0 ** -45, 1: 2.0 ** -52}     # one rounding of the variant
+POLY = {0: 1.1e-10, 1: 3.3e-13}                 # relative error of the weight's polynomial
+CARLSON = {0: 5e-10, 1: 1e-13}
+
+
+@pytest.fixture(scope="module")
+def areas(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("area") / "area.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-w", "-shared", "-fPIC", "-I", os.path.join(ROOT, "tests", "hip_shim"),
+                    "-I", os.path.join(ROOT, "paper_2609_29253_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "area_driver.cpp"), "-o", so], check=True)
+    fn = ctypes.CDLL(so).pair_areas
+    pd = ctypes.POINTER(ctypes.c_double)
+    fn.argtypes, fn.restype = [pd, pd, ctypes.c_double, ctypes.c_int, ctypes.c_int, ctypes.c_int, pd], ctypes.c_long
+
+    def run(tr, x, r0, lo, hi, kind):
+        out, t, v = np.zeros(hi - lo + 1), np.array(tr, float), np.array(x, float)
+        p = lambda a: a.ctypes.data_as(pd)  # noqa: E731
+        n = fn(p(t), p(v), r0, lo, hi, kind, p(out))
+        return out, n
+
+    return run
+
+
+def below(tr, x, r):
+    """Area nearer than r, 30 digits."""
+    x = [mp.mpf(float(v)) for v in x]
+    p = [mp.mpf(float(v)) for v in tr[1:]]
+    if tr[0] == 0:
+        k = r * r - x[2] ** 2
+        if k <= 0:
+            return mp.mpf(0)
+
+        def quarter(u, v):      # [0, u] x [0, v], u, v >= 0
+            w0, w1 = min(mp.sqrt(max(k - v * v, 0)), u), min(mp.sqrt(k), u)
+            F = lambda w: (w * mp.sqrt(max(k - w * w, 0)) + k * mp.asin(w / mp.sqrt(k))) / 2  # noqa: E731
+            return v * w0 + (F(w1) - F(w0) if w1 > w0 else 0)
+
+        return sum(a * b * mp.sign(a * p[0] - x[0]) * mp.sign(b * p[1] - x[1])
+                   * quarter(abs(a * p[0] - x[0]), abs(b * p[1] - x[1])) for a in (1, -1) for b in (1, -1))
+    R, th, hl = p
+    rho, phi = mp.hypot(x[0], x[1]), mp.atan2(x[1], x[0])
+    k = r * r - (R - rho) ** 2
+    if k <= 0:
+        return mp.mpf(0)
+    mu = 4 * R * rho
+    m = mu / k
+
+    def half(u):        # [0, u] x [-hl - z, hl - z], 0 <= u <= pi
+        s2 = mp.sin(u / 2) ** 2
+        amp = lambda q: mp.asin(mp.sqrt(min(max(q, 0) / mu, s2, mp.mpf(1))))  # noqa: E731
+        E = lambda t: mp.re(mp.ellipe(t, m))  # noqa: E731
+        b, t = amp(k), mp.mpf(0)
+        for v, sg in ((hl - x[2], 1), (-hl - x[2], -1)):
+            a = amp(k - v * v)
+            t += sg * mp.sign(v) * (abs(v) * 2 * a + 2 * mp.sqrt(k) * (E(b) - E(a)))
+        return t
+
+    t = mp.mpf(0)
+    for u, sg in ((th - phi, 1), (-th - phi, -1)):
+        q = abs(u)
+        t += sg * mp.sign(u) * (half(q) if q <= mp.pi else 2 * half(mp.pi) - half(2 * mp.pi - q))
+    return R * t
+
+
+def check(areas, tr, x, r0, carlson=False):
+    x = np.asarray(x, float)
+    if tr[0] == 0:
+        d = np.maximum(0, np.abs(x[:2]) - tr[1:3])
+        near = math.hypot(np.linalg.norm(d), x[2])
+        far = math.hypot(np.linalg.norm(np.abs(x[:2]) + tr[1:3]), x[2])
+        size = far ** 2 - x[2] ** 2
+    else:
+        R, th, hl = tr[1:]
+        rho, phi = math.hypot(x[0], x[1]), abs(math.atan2(x[1], x[0]))
+        psi = lambda u: (R - rho) ** 2 + 4 * R * rho * math.sin(u / 2) ** 2  # noqa: E731
+        near = math.sqrt(psi(max(phi - th, 0)) + max(abs(x[2]) - hl, 0) ** 2)
+        far = math.sqrt(psi(min(phi + th, math.pi)) + (abs(x[2]) + hl) ** 2)
+        size = (max(far ** 2 - (R - rho) ** 2, (R + rho) ** 2 - near ** 2, 1.0) + 4 * R * rho) * R / math.sqrt(4 * R * rho)
+    lo, hi = math.floor(near - r0), math.ceil(far - r0) + 1
+    full = {k: areas(tr, x, r0, lo, hi, k)[0] for k in (0, 1)}
+    top = full[1].max()
+    bins = sorted({*range(lo, min(lo + 4, hi)), *range(max(hi - 4, lo), hi + 1),
+                   *np.linspace(lo, hi, 7).round().astype(int).tolist()})
+    with mp.workdps(30):
+        at = lambda m: below(tr, x, mp.mpf(r0) + m)  # noqa: E731
+        ref = np.array([float(at(m) - at(m - 1)) for m in bins])
+        whole = float(at(hi) - at(lo - 1))
+    for kind, got in full.items():
+        tol = 64 * UNIT[kind] * (size + far ** 2 * 1e-3) / top + POLY[kind] + 1e-13
+        if carlson:
+            tol += CARLSON[kind] * size / top
+        err = np.abs(got[np.array(bins) - lo] - ref).max() / top
+        assert err <= tol, (tr, list(x), kind, err, tol)
+        assert abs(got.sum() - whole) <= (POLY[kind] + 64 * UNIT[kind]) * whole + tol * top, (tr, list(x), kind)
+        # a window that cuts the walk gives the same areas, bit for bit
+        a, b = lo + len(got) // 3, lo + (2 * len(got)) // 3
+        part, _ = areas(tr, x, r0, a, b, kind)
+        assert np.array_equal(part, got[a - lo:b - lo + 1])
+
+
+# half sides (in bins): around the tables' ranges and down to less than one bin
+@pytest.mark.parametrize("half", [(13.3, 13.3), (8.3, 50.0), (0.6, 0.4), (160.0, 3.0)])
+def test_planar_areas(areas, half):
+    rng = np.random.default_rng(3)
+    L1, L2 = half
+    spots = [(0.0, 0.0), (L1, L2), (0.0, -L2), (0.3 * L1, 0.9 * L2), (3 * L1, 0.2 * L2), (-2 * L1 - 40, 5 * L2 + 60)]
+    for u, v in spots + [tuple(rng.uniform(-200, 200, 2)) for _ in range(4)]:
+        check(areas, [0, L1, L2, 0], [u, v, rng.uniform(300, 900)], 250.25)
+
+
+# angular half-apertures on both sides of the polynomials' ranges, voxels in
+# front of, beside and behind the focal line and next to it
+@pytest.mark.parametrize("theta", [0.02, 0.12, 0.35, 1.4])
+@pytest.mark.parametrize("angle", [0.0, 0.05, 1.65, 3.1, math.pi])
+def test_cylinder_areas(areas, theta, angle):
+    rng = np.random.default_rng(5)
+    R, hl = 300.0, 21.0
+    for rho, z in ((150.0, 3.0), (60.0, 70.0), (4.0, 30.0), (0.01, 25.0)):
+        x = [rho * math.cos(angle), rho * math.sin(angle), z + rng.uniform(0, 1)]
+        # where the polynomials do not serve, Carlson's integral does
+        narrow = theta <= 0.12 and rho >= 60.0 and angle + theta < math.pi
+        check(areas, [1, R, theta, hl], x, 100.3, carlson=not narrow)
+
+
+def test_cylinder_areas_against_elliptic_integrals(areas):
+    """Random pairs: the sweep against Carlson's integral alone, whose areas have
+    its stated error; the same (quadrant, bin) pairs are visited."""
+    rng = np.random.default_rng(6)
+    for _ in range(300):
+        R = rng.uniform(100, 900)
+        tr = [1, R, rng.choice([rng.uniform(0.01, 0.2), rng.uniform(0.2, 1.5)]), rng.uniform(0.5, 80)]
+        rho, phi = R * 10 ** rng.uniform(-3, -0.1), rng.uniform(-math.pi, math.pi)
+        x = [rho * math.cos(phi), rho * math.sin(phi), rng.uniform(-200, 200)]
+        hi = int(R + rho + abs(x[2]) + tr[3]) + 3
+        ref, n = areas(tr, x, 0.4, 0, hi, 3)
+        size = (hi ** 2) * (R / math.sqrt(4 * R * rho))
+        for kind in (0, 1):
+            got, k = areas(tr, x, 0.4, 0, hi, kind)
+            assert k == n
+            tol = (64 * UNIT[kind] + CARLSON[kind]) * size / ref.max() + POLY[kind]
+            assert np.abs(got - ref).max() <= tol * ref.max(), (tr, x, kind)
