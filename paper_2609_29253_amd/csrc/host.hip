@@ -104,7 +104,7 @@ struct pat_ctx {
     int32_t* d_kperm = nullptr;
     double* d_scale = nullptr;
     double* d_G = nullptr;
-    double* d_qpts = nullptr;
+    double* d_qpts = nullptr;        // rows [K][n1][2], then columns [K][n2], of the quadrature points
     double* d_qdA = nullptr;
     double* d_f = nullptr;
     void* d_W = nullptr;
@@ -335,39 +335,28 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         }
         G[jj] = acc / p.U;
     }
-    // ---- quadrature points (midpoint tensor rule, barycentres of equal cells)
+    // ---- quadrature points (midpoint tensor rule, barycentres of equal cells), in
+    // the transducer's frame: rows of the first surface coordinate, columns of the second
     std::vector<double> qp, qdA;
-    int Q = 0;
-    if (p.area_mode == PAT_AREA_QUADRATURE) {
-        Q = p.quad_n1 * p.quad_n2;
-        qp.resize((size_t)K * Q * 3);
+    const size_t qn1 = p.quad_n1, qn2 = p.quad_n2;
+    const int Q = p.area_mode == PAT_AREA_QUADRATURE ? p.quad_n1 * p.quad_n2 : 0;
+    if (Q > 0) {
+        qp.resize((size_t)K * (2 * qn1 + qn2));
         qdA.resize(K);
         for (int k = 0; k < K; ++k) {
             const pat_transducer& t = tr[k];
-            double n3[3];
-            cross3(t.e1, t.e2, n3);
-            double* P = qp.data() + (size_t)k * Q * 3;
-            if (t.shape == PAT_PLANAR) {
-                double du = 2.0 * t.half_w / p.quad_n1, dv = 2.0 * t.half_h / p.quad_n2;
-                qdA[k] = du * dv / (dr * dr);
-                for (int a = 0; a < p.quad_n1; ++a)
-                    for (int b = 0; b < p.quad_n2; ++b) {
-                        double u = -t.half_w + (a + 0.5) * du, v = -t.half_h + (b + 0.5) * dv;
-                        for (int q = 0; q < 3; ++q)
-                            P[3 * (a * p.quad_n2 + b) + q] = (t.c0[q] + u * t.e1[q] + v * t.e2[q]) / dr;
-                    }
-            } else {
-                double dth = 2.0 * t.theta_max / p.quad_n1, dz = 2.0 * t.half_len / p.quad_n2;
-                qdA[k] = t.radius * dth * dz / (dr * dr);
-                for (int a = 0; a < p.quad_n1; ++a)
-                    for (int b = 0; b < p.quad_n2; ++b) {
-                        double th = -t.theta_max + (a + 0.5) * dth, z = -t.half_len + (b + 0.5) * dz;
-                        double cs = std::cos(th), sn = std::sin(th);
-                        for (int q = 0; q < 3; ++q)
-                            P[3 * (a * p.quad_n2 + b) + q] =
-                                (t.c0[q] + t.radius * cs * t.e2[q] + t.radius * sn * n3[q] + z * t.e1[q]) / dr;
-                    }
+            const bool flat = t.shape == PAT_PLANAR;
+            double* row = qp.data() + 2 * qn1 * k;
+            double* col = qp.data() + 2 * qn1 * K + qn2 * k;
+            const double h1 = flat ? t.half_w : t.theta_max, h2 = flat ? t.half_h : t.half_len;
+            const double d1 = 2.0 * h1 / p.quad_n1, d2 = 2.0 * h2 / p.quad_n2;
+            qdA[k] = (flat ? 1.0 : t.radius) * d1 * d2 / (dr * dr);
+            for (size_t a = 0; a < qn1; ++a) {
+                const double u = -h1 + (a + 0.5) * d1;
+                row[2 * a] = (flat ? u : t.radius * std::cos(u)) / dr;
+                row[2 * a + 1] = (flat ? 0.0 : t.radius * std::sin(u)) / dr;
             }
+            for (size_t b = 0; b < qn2; ++b) col[b] = (-h2 + (b + 0.5) * d2) / dr;
         }
     }
 
@@ -457,9 +446,11 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     B.nby = nby;
     B.nbz = nbz;
     B.N = N;
-    B.qpts = c->d_qpts;
+    B.qrow = c->d_qpts;
+    B.qcol = Q > 0 ? c->d_qpts + 2 * qn1 * K : nullptr;
     B.qdA = c->d_qdA;
-    B.Q = Q;
+    B.qn1 = Q > 0 ? p.quad_n1 : 0;
+    B.qn2 = Q > 0 ? p.quad_n2 : 0;
     B.lut = c->d_lut;
     Lp.ngroups = 0;
     int off = 0;

@@ -558,15 +558,33 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
 // quadrature over surface points (Alg. 2 / Alg. 6)
 // ---------------------------------------------------------------------------
 
-// bin of the distance sqrt(r2): [r0 + m - 1, r0 + m); FP32 estimate, FP64
-// decision.  The estimate is the one v_sqrt_f32 (1 ulp; the correctly rounded
-// sqrtf the compiler would emit costs some 15 more instructions per point): at
-// any distance here it lands within one bin of the true one, which the two FP64
-// comparisons then correct
-__device__ __forceinline__ int point_bin(double r2, double r0, float r0f)
+// The surface points of a transducer are a tensor grid in its frame: rows of the
+// first surface coordinate, each a point (X, Y) of two frame coordinates, times
+// columns of the second one along the third, so that a point's squared distance is
+// one FMA on top of its row's.
+// (Read through the constant address space: the same for every lane, so a scalar load.)
+typedef const __attribute__((address_space(4))) double ConstDouble;
+struct QuadFrame {
+    double p0, p1, pc;   // the voxel's coordinates against the rows and the columns
+    __device__ __forceinline__ QuadFrame(const TrDev& T, int ix, int iy, int iz)
+    {
+        double x[3];
+        frame_coords(T, ix, iy, iz, x);
+        p0 = x[0];
+        p1 = T.shape == 0 ? x[2] : x[1];
+        pc = T.shape == 0 ? x[1] : x[2];
+    }
+    __device__ __forceinline__ double row2(const ConstDouble* w) const
+    {
+        const double a = p0 - w[0], b = p1 - w[1];
+        return fma(a, a, b * b);
+    }
+};
+
+// bin of the distance sqrt(r2): [r0 + m - 1, r0 + m), decided in FP64
+__device__ __forceinline__ int point_bin(double r2, double r0)
 {
-    float rf = __builtin_amdgcn_sqrtf((float)r2);
-    int m = (int)floorf(rf - r0f) + 1;
+    const int m = (int)floor(sqrt64(r2) - r0) + 1;
     double e = r0 + (double)(m - 1);
     if (r2 < e * e) return m - 1;
     e += 1.0;
@@ -574,10 +592,48 @@ __device__ __forceinline__ int point_bin(double r2, double r0, float r0f)
     return m;
 }
 
-template <class AT> __device__ __forceinline__ AT inv_dist(double r2);
-template <> __device__ __forceinline__ float inv_dist<float>(double r2) { return __builtin_amdgcn_rsqf((float)r2); }
-template <> __device__ __forceinline__ double inv_dist<double>(double r2) { return rsq64(r2); }
+// the inverse distance of the weights
+template <class AT> __device__ __forceinline__ AT inv_dist(double r2, float inv);
+template <> __device__ __forceinline__ float inv_dist<float>(double, float inv) { return inv; }
+template <> __device__ __forceinline__ double inv_dist<double>(double r2, float) { return rsq64(r2); }
 
+// Half a bin less the error of the FP32 estimate of a distance below rmax
+// (2.8e-7 of it: conversions, v_rsq_f32, one FMA against the rounded r0)
+__device__ __forceinline__ float sure_half(double rmax) { return (float)(0.5 - 3e-7 * rmax); }
+
+// Bins and inverse distances of kQuadPoints points at squared distances row2 +
+// (pc - col)^2.  The FP32 distance decides the bin unless it falls within its
+// own error of an edge; then (in 6 % of the wave's steps at 2000 bins) the wave
+// decides in FP64.
+constexpr int kQuadPoints = 2;
+template <class AT, int G>
+__device__ __forceinline__ void quad_points(double row2, double pc, const ConstDouble* col, double r0,
+                                            float r0f, float half, int (&m)[G], AT (&inv)[G])
+{
+    double r2[G];
+    bool unsure = false;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const double d = pc - col[g];
+        r2[g] = fma(d, d, row2);
+        const float f = (float)r2[g], i = __builtin_amdgcn_rsqf(f);
+        const float t = fmaf(f, i, -r0f), fl = floorf(t);
+        m[g] = (int)fl + 1;
+        unsure |= !(fabsf((t - fl) - 0.5f) < half);
+        inv[g] = inv_dist<AT>(r2[g], i);
+    }
+    if (__any(unsure))
+#pragma unroll
+        for (int g = 0; g < G; ++g) m[g] = point_bin(r2[g], r0);
+}
+
+// Bound by VALU issue: per point two FP64 operations, one FP32 reciprocal root
+// for bin and weight, and the sink's.  Before, each point took six FP64
+// operations from its global coordinates and two FP64 comparisons of its bin.
+// 128^3 voxels x 256 cylinders x 16 x 16 points, FP32: A 141 -> 108 ms, A^T 103 ->
+// 63 ms; FP64: 159 -> 127, 140 -> 106; the same bins and weights bit for bit.  The
+// forward is left with its runs: in nearly every step some lane's run ends and
+// the wave steps through the flush.
 template <class AT, int NB, class Real>
 __global__ __launch_bounds__(kThreads) void k_fwd_quad(KParams P, const Real* __restrict__ coef,
                                                         double* __restrict__ f)
@@ -593,17 +649,19 @@ __global__ __launch_bounds__(kThreads) void k_fwd_quad(KParams P, const Real* __
         p0[b] = Bk.valid ? (double)coef[b * P.N + Bk.idx] : 0.0;
         nz |= p0[b] != 0.0;
     }
-    const double X0 = P.origin[0] + Bk.ix * P.w, X1 = P.origin[1] + Bk.iy * P.w, X2 = P.origin[2] + Bk.iz * P.w;
     if (!__syncthreads_or(nz)) return;
     const float r0f = (float)P.r0;
     const int kbeg = blockIdx.y * P.kchunk, kend = min(P.nk, kbeg + P.kchunk);
     for (int kk = kbeg; kk < kend; ++kk) {
         const int k = P.kperm[kk];
         const TrDev T = P.tr[k];
-        const double* __restrict__ Q = P.qpts + (int64_t)k * P.Q * 3;
+        const ConstDouble* row = (const ConstDouble*)(P.qrow + (int64_t)k * 2 * P.qn1);
+        const ConstDouble* col = (const ConstDouble*)(P.qcol + (int64_t)k * P.qn2);
         const AT dA = (AT)P.qdA[k];
+        const QuadFrame F(T, Bk.ix, Bk.iy, Bk.iz);
         int wlo, whi;
         brick_window(P, Bk, T, wlo, whi);
+        const float half = sure_half(P.r0 + whi + 1);
         for (int plo = wlo; plo <= whi; plo += HB) {
             const int phi = min(whi, plo + HB - 1);
             const int wn = phi - plo + 1;
@@ -612,26 +670,41 @@ __global__ __launch_bounds__(kThreads) void k_fwd_quad(KParams P, const Real* __
                 for (int b = 0; b < NB; ++b) hist[b * HB + i] = 0.0;
             __syncthreads();
             if (nz) {
-                int mcur = -(1 << 30);
+                // consecutive points in one bin add up in a register
+                int mcur = plo - 1;
                 AT acc = AT(0);
-                for (int q = 0; q < P.Q; ++q) {
-                    double dx = Q[3 * q] - X0, dy = Q[3 * q + 1] - X1, dz = Q[3 * q + 2] - X2;
-                    double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                    int m = point_bin(r2, P.r0, r0f);
-                    AT cv = dA * inv_dist<AT>(r2);
-                    if (m != mcur) {
-                        if (mcur >= plo && mcur <= phi)
+                auto flush = [&]() {
+                    if ((unsigned)(mcur - plo) < (unsigned)wn)
 #pragma unroll
-                            for (int b = 0; b < NB; ++b) atomicAdd(&hist[b * HB + (mcur - plo)], p0[b] * (double)acc);
+                        for (int b = 0; b < NB; ++b) atomicAdd(&hist[b * HB + (mcur - plo)], p0[b] * (double)acc);
+                };
+                auto add = [&](int m, AT cv) {
+                    if (m != mcur) {
+                        flush();
                         mcur = m;
                         acc = cv;
                     } else {
                         acc += cv;
                     }
-                }
-                if (mcur >= plo && mcur <= phi)
+                };
+                for (int a = 0; a < P.qn1; ++a) {
+                    const double r2 = F.row2(row + 2 * a);
+                    int q = 0;
+                    for (; q + kQuadPoints <= P.qn2; q += kQuadPoints) {
+                        int m[kQuadPoints];
+                        AT inv[kQuadPoints];
+                        quad_points<AT>(r2, F.pc, col + q, P.r0, r0f, half, m, inv);
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) atomicAdd(&hist[b * HB + (mcur - plo)], p0[b] * (double)acc);
+                        for (int g = 0; g < kQuadPoints; ++g) add(m[g], dA * inv[g]);
+                    }
+                    for (; q < P.qn2; ++q) {
+                        int m[1];
+                        AT inv[1];
+                        quad_points<AT>(r2, F.pc, col + q, P.r0, r0f, half, m, inv);
+                        add(m[0], dA * inv[0]);
+                    }
+                }
+                flush();
             }
             __syncthreads();
             const int64_t fo = (plo - P.Mlo);
@@ -659,16 +732,18 @@ __global__ __launch_bounds__(kThreads) void k_adj_quad(KParams P, const Real* __
     double acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = 0.0;
-    const double X0 = P.origin[0] + Bk.ix * P.w, X1 = P.origin[1] + Bk.iy * P.w, X2 = P.origin[2] + Bk.iz * P.w;
     const float r0f = (float)P.r0;
     const int kbeg = blockIdx.y * P.kchunk, kend = min(P.nk, kbeg + P.kchunk);
     for (int kk = kbeg; kk < kend; ++kk) {
         const int k = P.kperm[kk];
         const TrDev T = P.tr[k];
-        const double* __restrict__ Q = P.qpts + (int64_t)k * P.Q * 3;
+        const ConstDouble* row = (const ConstDouble*)(P.qrow + (int64_t)k * 2 * P.qn1);
+        const ConstDouble* col = (const ConstDouble*)(P.qcol + (int64_t)k * P.qn2);
         const AT dA = (AT)P.qdA[k];
+        const QuadFrame F(T, Bk.ix, Bk.iy, Bk.iz);
         int wlo, whi;
         brick_window(P, Bk, T, wlo, whi);
+        const float half = sure_half(P.r0 + whi + 1);
         for (int plo = wlo; plo <= whi; plo += HB) {
             const int phi = min(whi, plo + HB - 1);
             const int wn = phi - plo + 1;
@@ -682,14 +757,27 @@ __global__ __launch_bounds__(kThreads) void k_adj_quad(KParams P, const Real* __
                 AT part[NB];
 #pragma unroll
                 for (int b = 0; b < NB; ++b) part[b] = AT(0);
-                for (int q = 0; q < P.Q; ++q) {
-                    double dx = Q[3 * q] - X0, dy = Q[3 * q + 1] - X1, dz = Q[3 * q + 2] - X2;
-                    double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                    int m = point_bin(r2, P.r0, r0f);
-                    if (m < plo || m > phi) continue;
-                    AT cv = dA * inv_dist<AT>(r2);
+                auto add = [&](int m, AT cv) {
+                    if ((unsigned)(m - plo) >= (unsigned)wn) return;
 #pragma unroll
                     for (int b = 0; b < NB; ++b) part[b] = fma(cv, (AT)Ws[b * HB + (m - plo)], part[b]);
+                };
+                for (int a = 0; a < P.qn1; ++a) {
+                    const double r2 = F.row2(row + 2 * a);
+                    int q = 0;
+                    for (; q + kQuadPoints <= P.qn2; q += kQuadPoints) {
+                        int m[kQuadPoints];
+                        AT inv[kQuadPoints];
+                        quad_points<AT>(r2, F.pc, col + q, P.r0, r0f, half, m, inv);
+#pragma unroll
+                        for (int g = 0; g < kQuadPoints; ++g) add(m[g], dA * inv[g]);
+                    }
+                    for (; q < P.qn2; ++q) {
+                        int m[1];
+                        AT inv[1];
+                        quad_points<AT>(r2, F.pc, col + q, P.r0, r0f, half, m, inv);
+                        add(m[0], dA * inv[0]);
+                    }
                 }
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] += (double)part[b];
@@ -724,7 +812,7 @@ __global__ __launch_bounds__(kThreads) void k_count(KParams P, int quad, unsigne
     if (Bk.valid) {
         for (int kk = 0; kk < P.nk; ++kk) {
             const TrDev T = P.tr[P.kperm[kk]];
-            if (quad) { evals += P.Q; pairs += 1; continue; }
+            if (quad) { evals += P.qn1 * P.qn2; pairs += 1; continue; }
             double x[3];
             frame_coords(T, Bk.ix, Bk.iy, Bk.iz, x);
             const int lo = (int)P.Jlo, hi = (int)P.Jhi;

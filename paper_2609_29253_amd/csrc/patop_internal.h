@@ -59,9 +59,11 @@ struct KParams {
     // lookup-table I_l: {E~, F~} on the power-law grid, node (i, j) at j N + i
     const double2* lut;
     // quadrature
-    const double* qpts;     // [K][Q][3] global point coordinates
+    const double* qrow;     // [K][qn1][2] rows of the points: two frame coordinates (x1, x3 planar; x1, x2
+                            // cylinder)
+    const double* qcol;     // [K][qn2] columns: the frame coordinate along the other surface direction
     const double* qdA;      // [K] cell area (dr^2 units)
-    int32_t Q;
+    int32_t qn1, qn2;
 };
 
 }  // namespace patop
