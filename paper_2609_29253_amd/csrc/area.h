@@ -163,7 +163,7 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 // Lambda = int dw / y the angle (or hyperbolic angle) the arc subtends.  An error
 // eps of p changes each area by at most eps of itself, whatever the cancellation
 // between edges, and costs no elliptic integral: two square roots, one inverse
-// function and about 6 N + 40 further FP64 operations per edge, with no loop
+// function and about 6 N + 35 further FP64 operations per edge, with no loop
 // whose length differs between lanes.  A rectangle is the case h = 1, N = 0.
 //
 // End points of the arc: alpha starts clamped at the quadrant's near end N (u =
@@ -171,35 +171,80 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 // along v = c until the corner (F, c) and is then clamped at the far end F.
 
 // h's factor (1 - x)^(-1/2) = (1 - xc)^(-1/2) (1 - tau)^(-1/2), tau = (x - xc) /
-// (1 - xc): interpolant of degree N at Chebyshev nodes on |tau| <= eta, relative
-// error 1.1e-10 (N = 5), 5.7e-11 (8), 6.2e-14 (7), 3.3e-13 (10)
-template <int N> struct Weight;
-template <> struct Weight<5> {
-    static constexpr double eta = 0.05;
-    static constexpr double c[] = {1.0000000001105098, 0.500000000102622, 0.3749992044251002, 0.3124992612121438,
-                                   0.274285523209855, 0.2468812331229099};
+// (1 - xc): interpolant of degree N at Chebyshev nodes on |tau| <= eta, of relative
+// error 1.6e-9 (N = 4) and 7.5e-10 (7) for FP32 input and output, whose signals
+// round at 6e-8 and to which these errors pass undivided (each bin's area changes
+// by that share), and 6.2e-14 (7) and 3.3e-13 (10) for FP64.
+template <int NW, bool WIDE> struct Weight;
+template <> struct Weight<1, false> {
+    static constexpr int n = 4;
+    static constexpr double eta = 0.04;
+    static constexpr double c[n + 1] = {
+        1.0, 0.4999998027893683, 0.3749998192165893, 0.31299285870394444, 0.2738893011398508};
 };
-template <> struct Weight<8> {
+template <> struct Weight<1, true> {
+    static constexpr int n = 7;
     static constexpr double eta = 0.16;
-    static constexpr double c[] = {1.0, 0.49999999704787307, 0.3749999971941834, 0.3125015348867947,
-                                   0.27343895879424956, 0.2458789227748675, 0.2253817687557605,
-                                   0.22053917177169305, 0.20689706937941357};
+    static constexpr double c[n + 1] = {
+        0.9999999993097828, 0.49999999934780515, 0.375000862151671, 0.31250081465170293, 0.27326976417167687,
+        0.24593526203177093, 0.23596719691165274, 0.21928054205212558};
 };
-template <> struct Weight<7> {
+template <> struct Weight<2, false> {
+    static constexpr int n = 7;
     static constexpr double eta = 0.05;
-    static constexpr double c[] = {0.9999999999999398, 0.49999999999994316, 0.37500000077050993,
-                                   0.31250000072773826, 0.27343595956342226, 0.24609229508034408,
-                                   0.2265708771687404, 0.21040290777839668};
+    static constexpr double c[n + 1] = {
+        0.9999999999999398, 0.49999999999994316, 0.37500000077050993, 0.31250000072773826, 0.27343595956342226,
+        0.24609229508034408, 0.2265708771687404, 0.21040290777839668};
 };
-template <> struct Weight<10> {
+template <> struct Weight<2, true> {
+    static constexpr int n = 10;
     static constexpr double eta = 0.16;
-    static constexpr double c[] = {1.0, 0.5000000000212094, 0.3750000000203339, 0.31249998344974184,
-                                   0.2734374841330066, 0.2460973593854478, 0.2255893978103804, 0.20915235533051377,
-                                   0.19607355491324047, 0.1978170102153056, 0.1880321370533884};
+    static constexpr double c[n + 1] = {
+        1.0, 0.5000000000212094, 0.3750000000203339, 0.31249998344974184, 0.2734374841330066,
+        0.2460973593854478, 0.2255893978103804, 0.20915235533051377, 0.19607355491324047, 0.1978170102153056,
+        0.1880321370533884};
+};
+
+// Lambda's inverse function f, f(x) = x + x^3 P(x^2): P by interpolation at Chebyshev
+// nodes of x^2, for atan (S = 1) and atanh (S = -1), on x <= 1/8 and on x <=
+// 0.42; relative error 2e-15 and 1.3e-13 (NW = 1), 7e-18 and 5e-17 (NW = 2)
+template <int S, int NW> struct ArcSeries;
+template <> struct ArcSeries<1, 1> {
+    static constexpr double lo[5] = {
+        -0.33333333333319803, 0.19999999956695652, -0.14285692082379586, 0.11107119763160542,
+        -0.08796919798324465};
+    static constexpr double hi[8] = {
+        -0.3333333333325081, 0.19999999940043187, -0.14285707102889028, 0.11110781342546695,
+        -0.09083412043223445, 0.0759848113690192, -0.05998786787867099, 0.03245379438372544};
+};
+template <> struct ArcSeries<1, 2> {
+    static constexpr double lo[6] = {
+        -0.33333333333333287, 0.19999999999790477, -0.14285714129116034, 0.1111106826170422,
+        -0.09085599506798686, 0.07387718384425714};
+    static constexpr double hi[11] = {
+        -0.3333333333333333, 0.19999999999994217, -0.14285714284398277, 0.11111110993987848,
+        -0.09090903726254194, 0.0769216368130413, -0.06664240513226126, 0.05855828347679443,
+        -0.05073475931846312, 0.03889055030264144, -0.018764922473679908};
+};
+template <> struct ArcSeries<-1, 1> {
+    static constexpr double lo[5] = {
+        0.3333333333334781, 0.19999999953686995, 0.1428573796423765, 0.11106881256020994, 0.09398126834838963};
+    static constexpr double hi[9] = {
+        0.3333333333334639, 0.19999999988024808, 0.14285716086836603, 0.1111100729792487, 0.09093888604356387,
+        0.07644687050656893, 0.0710737704056635, 0.03570834279784205, 0.11354190728849271};
+};
+template <> struct ArcSeries<-1, 2> {
+    static constexpr double lo[6] = {
+        0.3333333333333328, 0.20000000000227505, 0.14285714116012183, 0.11111157356123932, 0.09085223469123827,
+        0.08013059813075277};
+    static constexpr double hi[11] = {
+        0.3333333333333336, 0.19999999999964782, 0.1428571429367304, 0.11111110411784622, 0.09090940491443848,
+        0.0769148899584336, 0.06679888190163528, 0.05746567311921013, 0.06144227524817444,
+        0.013262917513335266, 0.11309973802991415};
 };
 
 // atan(k / 32) and log(1 + k / 32), k = 0..32: the work-group copies them to LDS
-// (kArcTab doubles), so that Lambda costs one division and a short series
+// (kArcTab doubles) for the arguments above those
 constexpr int kArcNodes = 33;
 constexpr int kArcTab = 2 * kArcNodes;
 static __device__ const double kArcTable[kArcTab] = {
@@ -219,26 +264,39 @@ static __device__ const double kArcTable[kArcTab] = {
     0.661398482245365, 0.6773988235918061, 0.6931471805599453,
 };
 
-// X -+ X^3/3 + X^5/5 ... of a reduced argument |X| <= 1/64 (S = +1 atan, -1
-// atanh).  NW = 1: the terms after X in FP32 (<= 1.3e-6, so 8e-14 absolute)
 template <int S, int NW>
 __device__ __forceinline__ double arc_series(double X)
 {
-    if (NW == 1) {
-        const float xf = (float)X, u = xf * xf;
-        const float p = fmaf(u, 0.2f, S > 0 ? -1.0f / 3 : 1.0f / 3);
-        return X + (double)(xf * u * p);
-    }
+    // X -+ X^3/3 + X^5/5 ... (S = +1 atan, -1 atanh) of a table's rest, |X| <= 1/64
     const double u = X * X;
-    double p = fma(u, S > 0 ? -1.0 / 7 : 1.0 / 7, 1.0 / 5);
+    double p = NW == 1 ? 1.0 / 5 : fma(u, S > 0 ? -1.0 / 7 : 1.0 / 7, 1.0 / 5);
     p = fma(u, p, S > 0 ? -1.0 / 3 : 1.0 / 3);
     return fma(X * u, p, X);
+}
+
+// x + x^3 P(x^2)
+template <int M>
+__device__ __forceinline__ double arc_series(double x, const double (&c)[M])
+{
+    const double u = x * x;
+    double p = c[M - 1];
+#pragma unroll
+    for (int j = M - 2; j >= 0; --j) p = fma(p, u, c[j]);
+    return fma(x * u, p, x);
 }
 
 // 1/x to the accuracy of the variant: one Newton step on the FP32 seed, or two
 // on the FP64 one
 template <int NW>
 __device__ __forceinline__ double rcp_nw(double x) { return NW >= 2 ? rcp64_full(x) : rcp64<1>(x); }
+
+// num / den to the accuracy of the variant
+template <int NW>
+__device__ __forceinline__ double arc_quotient(double num, double den)
+{
+    const double r = NW >= 2 ? rcp64(den) : rcp_seed<1>(den), q = num * r;
+    return fma(fma(-q, den, num), r, q);
+}
 
 // atan(num / den), num >= 0, den > 0, num <= den (beyond it only by rounding): the node k / 32 next to
 // the quotient, by its FP32 estimate, and the series at the tangent of the rest
@@ -304,21 +362,49 @@ template <int N, int S, int NW>
 __device__ __forceinline__ double arc_edge(const ArcQuad<N>& q, double r, const double* tab)
 {
     const double K = fma(r, r, -q.base2);
-    const double od = K - q.d2, oc = K - q.c2;
-    const bool onD = od > q.oN, onC = oc < q.oF;
-    const double oa = fmax(od, q.oN), ob = fmin(oc, q.oF);
-    const double ra = sqrt64<NW>(onD ? (S > 0 ? od : -od) : K - q.oN);
-    const double rb = sqrt64<NW>(onC ? (S > 0 ? oc : -oc) : K - q.oF);
+    bool onD, onC;
+    double oa, ob, ea, eb;   // om at the end points, and the squares of what the roots give
+    if constexpr (N == 0) {
+        onD = K > q.oN + q.d2;
+        onC = K < q.oF + q.c2;
+        ea = K - (onD ? q.d2 : q.oN);
+        eb = K - (onC ? q.c2 : q.oF);
+        oa = ob = 0.0;
+    } else {
+        const double od = K - q.d2, oc = K - q.c2;
+        onD = od > q.oN;
+        onC = oc < q.oF;
+        oa = fmax(od, q.oN);
+        ob = fmin(oc, q.oF);
+        ea = onD ? S * od : K - q.oN;
+        eb = onC ? S * oc : K - q.oF;
+    }
+    const double ra = sqrt64<NW>(ea), rb = sqrt64<NW>(eb);
     const double wa = onD ? ra : q.wN, ya = onD ? q.d : ra;
     const double wb = onC ? rb : q.wF, yb = onC ? q.c : rb;
-    double lam;   // Lambda
-    if (S > 0)    // twice the half angle, so that the denominator stays positive
-        lam = 2.0 * arc_atan<NW>(fma(wb, ya, -wa * yb), K + fma(wa, wb, ya * yb), tab);
+    // Lambda: twice atan or atanh of num / den, the half angle, whose denominator
+    // stays positive.  The branches are the wave's: on 256^3 voxels x 512 rectangles
+    // nearly all arguments are below 1/8 (median 0.03), on 128^3 x 256 cylinders
+    // below 0.42 (median 0.14)
+    double num, den;
+    if (S > 0) {
+        num = fma(wb, ya, -wa * yb);
+        den = K + fma(wa, wb, ya * yb);
+    } else {
+        num = (wb + yb) - (wa + ya);
+        den = (wb + yb) + (wa + ya);
+    }
+    const double x = arc_quotient<NW>(num, den);
+    double lam;   // Lambda / 2
+    if (__any(!(fabs(x) <= 0.42)))
+        lam = S > 0 ? arc_atan<NW>(num, den, tab) : -0.5 * arc_log<NW>(wa + ya, wb + yb, tab);
+    else if (__any(fabs(x) > 0.125))
+        lam = arc_series(x, ArcSeries<S, NW>::hi);
     else
-        lam = -arc_log<NW>(wa + ya, wb + yb, tab);
+        lam = arc_series(x, ArcSeries<S, NW>::lo);
     if constexpr (N == 0) {
         const double Ba = wa * fma(ya, q.P[0], -q.d * q.Q[0]);
-        return fma(q.P[0] * K, lam, fma(wb, fma(yb, q.P[0], -q.c * q.Q[0]), -Ba));
+        return fma(q.Q[0] * K, lam, fma(wb, fma(yb, q.P[0], -q.c * q.Q[0]), -Ba));   // Q = 2 P
     } else {
         // (2j + 2) D[j] = p_j + (2j + 1) K D[j + 1]: the sum of p_j J_j is
         // D[0] (w y + K Lambda) - w y^3 (D[1] + D[2] om + ...)
@@ -328,7 +414,7 @@ __device__ __forceinline__ double arc_edge(const ArcQuad<N>& q, double r, const 
         for (int j = N; j > 0; --j) D[j - 1] = fma(K * ((2.0 * j - 1.0) / (2.0 * j)), D[j], q.P[j - 1]);
         const double Ba = wa * fma(ya, fma(-ya * ya, horner<N - 1>(D + 1, oa), D[0]), -q.d * horner<N>(q.Q, oa));
         const double Bb = wb * fma(yb, fma(-yb * yb, horner<N - 1>(D + 1, ob), D[0]), -q.c * horner<N>(q.Q, ob));
-        return fma(D[0] * K, lam, Bb - Ba);
+        return fma(D[0] * (K + K), lam, Bb - Ba);
     }
 }
 
@@ -344,10 +430,12 @@ __device__ __forceinline__ void arc_sweep(const ArcQuad<N>& q, double r0, int wl
     if (mb > me) return;
     const bool tail = me == q.mlast;
     const int mend = tail ? me - 1 : me;   // the last edge evaluated
-    double s0 = q.S0;
-    for (int m = mb > q.mfirst ? mb - 1 : mb; m <= mend; ++m) {
-        const double s1 = arc_edge<N, S, NW>(q, r0 + m, tab);
-        if (m >= mb) sink(m, s1 - s0);
+    double s0 = q.S0, r = r0 + mb;
+    if (mb > q.mfirst) s0 = arc_edge<N, S, NW>(q, r - 1.0, tab);
+    for (int m = mb; m <= mend; ++m, r += 1.0) {
+        const auto w = sink.fetch(m);   // what the bin's sum needs from memory, under way while the edge is evaluated
+        const double s1 = arc_edge<N, S, NW>(q, r, tab);
+        sink.add(m, s1 - s0, w);
         s0 = s1;
     }
     if (tail) sink(me, q.S1 - s0);
@@ -365,9 +453,10 @@ struct CyPair {
 
 // how the cylinder's I_l is evaluated
 enum : int {
-    kIlExact = 0,       // Carlson, Eq. cyl_Il
+    kIlExact = 0,       // exact (as weighted areas where they serve, in the pair sweeps)
     kIlTrapezoid = 1,   // chord of the level curve, Eq. trapezoid_Il
     kIlTable = 2,       // lookup tables of E~ and F~ (Sec. 4.2, LUT paragraph)
+    kIlCarlson = 3,     // exact, by Carlson's integral for every pair, Eq. cyl_Il
 };
 
 struct CyQuad {

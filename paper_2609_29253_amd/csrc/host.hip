@@ -21,6 +21,7 @@
 
 #include "geometry.h"
 #include "kernels.h"
+#include "pairs.h"
 #include "patop.h"
 
 using namespace patop;
@@ -153,6 +154,35 @@ void free_dev(pat_ctx* c)
     }
     c->ready = false;
     c->ws_bytes = 0;
+}
+
+// The share of the cylinders' pairs that the weighted areas serve with FP64 input
+// and output (arc_fit), on 4 x 4 x 4 voxels spread over the grid.  Below 0.4 the
+// kernels that evaluate every pair by Carlson's integral are faster, since waves
+// that hold both kinds of pair step through both (A + A^T on 61 x 47 x 53 voxels x
+// 96 cylinders, where 0.3 are served: 8.7 against 8.45 ms; a scan whose focal
+// lines cross the volume, 0.95 served: 16.5 against 21.9).
+double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& grid)
+{
+    int64_t fit = 0;
+    for (int i = 0; i < n; ++i) {
+        const TrDev& t = T[perm[i]];
+        for (int v = 0; v < 64; ++v) {
+            double x[3];
+            for (int a = 0; a < 3; ++a) {
+                x[a] = t.base[a];
+                for (int q = 0; q < 3; ++q) x[a] += t.g[a][q] * (double)(grid.n[q] - 1) * (((v >> (2 * q)) & 3) + 0.5) / 4.0;
+            }
+            const double rho = std::hypot(x[0], x[1]), ct = rho > 0.0 ? x[0] / rho : 1.0, st = rho > 0.0 ? std::fabs(x[1]) / rho : 0.0;
+            const double cm = ct * t.cth + st * t.sth, sm = st * t.cth - ct * t.sth;
+            const double cp = ct * t.cth - st * t.sth, sp = st * t.cth + ct * t.sth;
+            const bool in0 = sm < 0.0, inpi = !in0 && sp < 0.0;
+            fit += arc_fit<2>(t.p[0], rho, in0 ? 1.0 : inpi ? cp : cm, in0 ? cm : inpi ? -1.0 : cp, cm, cp, true, in0 || inpi,
+                              std::fabs(x[2]) + t.p[2], inpi)
+                       .fits;
+        }
+    }
+    return (double)fit / (64.0 * n);
 }
 
 struct DevGuard {
@@ -365,7 +395,11 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     const int nby = (int)((grid->n[1] + kBrickY - 1) / kBrickY);
     const int nbz = (int)((grid->n[2] + kBrickZ - 1) / kBrickZ);
     const int nbricks = nbx * nby * nbz;
-    const int target_wg = 4096;
+    // Work-groups of a brick's size that a launch is split into at least, by chunks
+    // of transducers.  The closed-form forward adds into f with atomics whatever
+    // its chunks, and four times as many shorten its last round (128^3 x 256
+    // cylinders 77.8 -> 75.2 ms); the adjoint stays in one chunk where it can, so that each voxel's sum has one order.
+    const int target_wg = 4096, target_fwd = surface ? 16384 : target_wg;
 
     // ---- device allocations
     const size_t rs = p.precision == PAT_FP64 ? sizeof(double) : sizeof(float);
@@ -461,9 +495,14 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.shape = s;
         Gp.kperm = c->d_kperm + off;
         Gp.nk = nk;
-        int nchunks = std::max(1, std::min(nk, (target_wg + nbricks - 1) / nbricks));
-        Gp.kchunk_fwd = (nk + nchunks - 1) / nchunks;
-        Gp.kchunk_adj = Gp.kchunk_fwd;
+        auto chunk = [&](int target) {
+            const int nchunks = std::max(1, std::min(nk, (target + nbricks - 1) / nbricks));
+            return (nk + nchunks - 1) / nchunks;
+        };
+        Gp.kchunk_fwd = chunk(target_fwd);
+        Gp.kchunk_adj = chunk(target_wg);
+        Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
+                     arc_share(T.data(), perm.data() + off, nk, *grid) < 0.4;
         off += nk;
     }
     Lp.nbricks = nbricks;

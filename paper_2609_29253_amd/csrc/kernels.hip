@@ -137,10 +137,11 @@ __device__ __forceinline__ void brick_window(const KParams& P, const Brick& Bk, 
 // the frame coordinates and cos / sin of theta_max, with no angle computed.
 // floor / ceil keep a shell of margin for rounding: [lo, hi] holds every bin of
 // every quadrant sweep of the pair.
+template <int SHAPE>
 __device__ __forceinline__ void pair_range(const TrDev& T, const double x[3], double r0, int& lo, int& hi)
 {
     double dmin2, dmax2;
-    if (T.shape == 0) {
+    if (SHAPE == 0) {
         const double du = fmax(0.0, fabs(x[0]) - T.p[0]), dv = fmax(0.0, fabs(x[1]) - T.p[1]);
         const double eu = fabs(x[0]) + T.p[0], ev = fabs(x[1]) + T.p[1];
         const double z2 = x[2] * x[2];
@@ -149,7 +150,7 @@ __device__ __forceinline__ void pair_range(const TrDev& T, const double x[3], do
     } else {
         const double R = T.p[0], ax1 = fabs(x[1]);
         const double rho2 = fma(x[0], x[0], x[1] * x[1]);
-        const double rho = sqrt(rho2);
+        const double rho = sqrt64<1>(rho2);
         const bool inside = fma(x[0], T.sth, -ax1 * T.cth) >= 0.0;   // |theta_i| <= theta_max
         const double cmin = inside ? rho : fma(x[0], T.cth, ax1 * T.sth);
         const double cmax = x[0] < -T.cth * rho ? -rho : fma(x[0], T.cth, -ax1 * T.sth);
@@ -158,35 +159,32 @@ __device__ __forceinline__ void pair_range(const TrDev& T, const double x[3], do
         dmin2 = fma(vmin, vmin, fma(-2.0 * R, cmin, base));
         dmax2 = fma(vmax, vmax, fma(-2.0 * R, cmax, base));
     }
-    lo = (int)floor(sqrt(fmax(dmin2, 0.0)) - r0);
-    hi = (int)ceil(sqrt(fmax(dmax2, 0.0)) - r0) + 1;
+    // FP32 roots (off by less than 2e-7), moved outward by twice that
+    lo = (int)floor((double)(sqrt_t((float)dmin2) * (1.0f - 4e-7f)) - r0);
+    hi = (int)ceil((double)(sqrt_t((float)dmax2) * (1.0f + 4e-7f)) - r0) + 1;
+}
+
+// minimum of v over the 64 lanes, all active, as a scalar: shifts by 1, 2, 4 and 8
+// within rows of 16 lanes, then two broadcasts across rows, each fused with its
+// minimum (a permute through LDS per step takes four times the instructions)
+__device__ __forceinline__ int wave_min(int v)
+{
+    constexpr int none = 0x7fffffff;
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x111, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x112, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x114, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x118, 0xf, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x142, 0xa, 0xf, false));
+    v = min(v, __builtin_amdgcn_update_dpp(none, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 // [min lo, max hi] over the lanes of the wave that take part (others pass
 // INT_MAX / INT_MIN), clipped to the kept shells [Jlo, Jhi]
 __device__ __forceinline__ void wave_window(const KParams& P, int lo, int hi, int& wlo, int& whi)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo = min(lo, __shfl_xor(lo, o));
-        hi = max(hi, __shfl_xor(hi, o));
-    }
-    wlo = (int)max((int64_t)lo, P.Jlo);
-    whi = (int)min((int64_t)hi, P.Jhi);
-}
-
-// frame coordinates of a voxel (Sec. 4.1 / Sec. 4.2 frames), FP64
-__device__ __forceinline__ void frame_coords(const TrDev& T, int ix, int iy, int iz, double x[3])
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) x[a] = fma(T.g[a][0], ix, fma(T.g[a][1], iy, fma(T.g[a][2], iz, T.base[a])));
-}
-
-// the work-group's copy of kArcTable (no barrier here)
-template <int STRIDE>
-__device__ __forceinline__ void load_arc_table(double* tab)
-{
-    for (int i = threadIdx.x; i < kArcTab; i += STRIDE) tab[i] = kArcTable[i];
+    wlo = max(wave_min(lo), (int)P.Jlo);
+    whi = min(~wave_min(~hi), (int)P.Jhi);
 }
 
 // ---------------------------------------------------------------------------
@@ -224,14 +222,100 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LDS window of a one-wave work-group, in bytes, shared by its volumes: with
-// sixteen of them per CU (four waves per SIMD) each may hold 10 KB; the
-// cylinder kernels also keep their 4 KB table of interval ends there
+// LDS window of a one-wave work-group, in bytes, shared by its volumes.  Planar:
+// with the arc table 7568 bytes, so that twenty-one of them fit a CU (the kernels
+// run at five waves per SIMD).  Cylinders keep their 4 KB table of interval ends
+// there too and run sixteen per CU.
 template <int SHAPE>
 constexpr int wave_window_bytes()
 {
-    return SHAPE == 1 ? 4096 : 8192;
+    return SHAPE == 1 ? 4096 : 7040;
 }
+
+// Where a sweep's areas go.  fetch(m) reads what bin m's sum needs, before the area
+// is known; add(m, area, fetched) finishes it.  give() and take() carry the sink to
+// and from a function that is not inlined.
+
+__device__ __forceinline__ void lds_add(double* p, double v)
+{
+    __builtin_amdgcn_ds_atomic_fadd_f64((LdsDouble*)p, v);
+}
+__device__ __forceinline__ void lds_add(LdsDouble* p, double v) { __builtin_amdgcn_ds_atomic_fadd_f64(p, v); }
+
+// forward: p0 * area into the LDS histogram of each volume (`stride` bins apart)
+template <int NB, class Ptr = double*>
+struct Scatter {
+    Ptr hist;
+    int stride, first;
+    double p0[NB];
+    __device__ __forceinline__ int fetch(int) const { return 0; }
+    __device__ __forceinline__ void add(int m, double area, int)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) lds_add(&hist[b * stride + (m - first)], p0[b] * area);
+    }
+    __device__ __forceinline__ void operator()(int m, double area) { add(m, area, 0); }
+    __device__ __forceinline__ Scatter<NB, LdsDouble*> give() const
+    {
+        Scatter<NB, LdsDouble*> s;
+        s.hist = (LdsDouble*)hist;
+        s.stride = stride;
+        s.first = first;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) s.p0[b] = p0[b];
+        return s;
+    }
+    __device__ __forceinline__ void take(const Scatter<NB, LdsDouble*>&) {}
+};
+
+// adjoint: area times each volume's W, summed
+template <int NB, class AT, class Real, class Ptr = const Real*>
+struct Gather {
+    using Lds = const __attribute__((address_space(3))) Real*;
+    Ptr Ws;
+    int stride, first;
+    AT part[NB];
+    struct Vals {
+        Real w[NB];
+    };
+    __device__ __forceinline__ Vals fetch(int m) const
+    {
+        Vals v;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) v.w[b] = Ws[b * stride + (m - first)];
+        return v;
+    }
+    __device__ __forceinline__ void add(int, double area, const Vals& v)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) part[b] = fma((AT)area, (AT)v.w[b], part[b]);
+    }
+    __device__ __forceinline__ void operator()(int m, double area) { add(m, area, fetch(m)); }
+    __device__ __forceinline__ Gather<NB, AT, Real, Lds> give() const
+    {
+        Gather<NB, AT, Real, Lds> s;
+        s.Ws = (Lds)Ws;
+        s.stride = stride;
+        s.first = first;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) s.part[b] = part[b];
+        return s;
+    }
+    __device__ __forceinline__ void take(const Gather<NB, AT, Real, Lds>& s)
+    {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) part[b] = s.part[b];
+    }
+};
+
+struct Count {
+    int n;
+    __device__ __forceinline__ int fetch(int) const { return 0; }
+    __device__ __forceinline__ void add(int, double, int) { ++n; }
+    __device__ __forceinline__ void operator()(int, double) { ++n; }
+    __device__ __forceinline__ Count give() const { return *this; }
+    __device__ __forceinline__ void take(const Count& s) { n = s.n; }
+};
 
 // The wave's 64 voxels (one per lane; `valid` false for lanes without one)
 // against transducers kperm[kbeg .. kend): per transducer the window is the
@@ -260,13 +344,13 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
         const int k = P.kperm[kk];
         int wlo, whi;
         typename PairOf<SHAPE, Real, IL, kWave>::type pair;
-        pair.bind(box, P.lut, tab);
+        pair.bind(box, P.lut, tab, P.tr + k, ix, iy, iz);
         {
             const TrDev T = P.tr[k];
             double x[3];
             frame_coords(T, ix, iy, iz, x);
             int lo = 0x7fffffff, hi = -0x7fffffff - 1;
-            if (nz) pair_range(T, x, P.r0, lo, hi);   // lanes whose volumes are all zero add nothing
+            if (nz) pair_range<SHAPE>(T, x, P.r0, lo, hi);   // lanes whose volumes are all zero add nothing
             wave_window(P, lo, hi, wlo, whi);
             pair.setup(T, x, P.r0);
         }
@@ -278,15 +362,17 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
                 for (int b = 0; b < NB; ++b) hist[b * HW + i] = 0.0;
             wave_lds_order();
             if (nz) {
-                auto sink = [&](int m, auto area) {
+                Scatter<NB> sink;
+                sink.hist = hist;
+                sink.stride = HW;
+                sink.first = plo;
 #pragma unroll
-                    for (int b = 0; b < NB; ++b) atomicAdd(&hist[b * HW + (m - plo)], p0[b] * (double)area);
-                };
+                for (int b = 0; b < NB; ++b) sink.p0[b] = p0[b];
                 pair.sweep(plo, phi, sink, P.r0);
             }
             wave_lds_order();
             for (int i = l; i < wn * S; i += kWave) {
-                const int jj = i / S;
+                const int jj = S == 1 ? i : i / S;   // (no division on the fine grid)
                 const int64_t m = (int64_t)(plo + jj - 1) * S + 1 + (i - jj * S);
                 if (m < P.Mlo || m > Mhi) continue;
 #pragma unroll
@@ -410,7 +496,7 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
             }
             if (!__syncthreads_or(nz)) continue;
             typename PairOf<SHAPE, Real, IL>::type pair;
-            pair.bind(box, P.lut, tab);
+            pair.bind(box, P.lut, tab, P.tr + k, Bk.ix, Bk.iy, Bk.iz);
             {
                 const TrDev T = P.tr[k];
                 double x[3];
@@ -418,10 +504,12 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
                 pair.setup(T, x, P.r0);
             }
             if (nz) {
-                auto sink = [&](int m, auto area) {
+                Scatter<NB> sink;
+                sink.hist = hist;
+                sink.stride = tile;
+                sink.first = tlo;
 #pragma unroll
-                    for (int v = 0; v < NB; ++v) atomicAdd(&hist[v * tile + (m - tlo)], p0[v] * (double)area);
-                };
+                for (int v = 0; v < NB; ++v) sink.p0[v] = p0[v];
                 // every edge is evaluated on its own (those outside a quadrant
                 // are set, as in the cube forward), so a tile's areas are the
                 // cube forward's; a cylinder wave's choice between the degrees
@@ -505,13 +593,13 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
         const int k = P.kperm[kk];
         int wlo, whi;
         typename PairOf<SHAPE, Real, IL, kWave>::type pair;
-        pair.bind(box, P.lut, tab);
+        pair.bind(box, P.lut, tab, P.tr + k, ix, iy, iz);
         {
             const TrDev T = P.tr[k];
             double x[3];
             frame_coords(T, ix, iy, iz, x);
             int lo = 0x7fffffff, hi = -0x7fffffff - 1;
-            if (valid) pair_range(T, x, P.r0, lo, hi);
+            if (valid) pair_range<SHAPE>(T, x, P.r0, lo, hi);
             wave_window(P, lo, hi, wlo, whi);
             pair.setup(T, x, P.r0);
         }
@@ -533,16 +621,15 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
                 }
             wave_lds_order();
             if (valid) {
-                AT part[NB];
+                Gather<NB, AT, Real> sink;
+                sink.Ws = Ws;
+                sink.stride = HB;
+                sink.first = plo;
 #pragma unroll
-                for (int b = 0; b < NB; ++b) part[b] = AT(0);
-                auto sink = [&](int m, auto area) {
-#pragma unroll
-                    for (int b = 0; b < NB; ++b) part[b] = fma((AT)area, (AT)Ws[b * HB + (m - plo)], part[b]);
-                };
+                for (int b = 0; b < NB; ++b) sink.part[b] = AT(0);
                 pair.sweep(plo, phi, sink, P.r0);
 #pragma unroll
-                for (int b = 0; b < NB; ++b) acc[b] += (double)part[b];
+                for (int b = 0; b < NB; ++b) acc[b] += (double)sink.part[b];
             }
         }
     }
@@ -816,13 +903,12 @@ __global__ __launch_bounds__(kThreads) void k_count(KParams P, int quad, unsigne
             double x[3];
             frame_coords(T, Bk.ix, Bk.iy, Bk.iz, x);
             const int lo = (int)P.Jlo, hi = (int)P.Jhi;
-            int nb = 0;
-            auto sink = [&](int, auto) { ++nb; };
+            Count sink{0};
             typename PairOf<SHAPE, double, kIlExact>::type pair;
-            pair.bind(box, nullptr, tab);
+            pair.bind(box, nullptr, tab, P.tr + P.kperm[kk], Bk.ix, Bk.iy, Bk.iz);
             pair.setup(T, x, P.r0);
             pair.sweep(lo, hi, sink, P.r0);
-            evals += nb;
+            evals += sink.n;
             pairs += 1;
         }
     }
@@ -1029,23 +1115,49 @@ hipError_t fwd_tile_nb(int nb, const KParams& P, const int32_t* items, int nitem
 }
 
 template <class Real>
-hipError_t fwd_tile_cyl(int mode, int nb, const KParams& P, const int32_t* items, int nitems, int tile, int ntiles,
+hipError_t fwd_tile_cyl(int mode, bool carlson, int nb, const KParams& P, const int32_t* items, int nitems, int tile, int ntiles,
                         int nbricks, const Real* coef, double* f, hipStream_t s)
 {
     if (mode == 2)
         return fwd_tile_nb<1, double, Real, kIlTrapezoid>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
     if (mode == 3)
         return fwd_tile_nb<1, double, Real, kIlTable>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
+    if constexpr (sizeof(Real) == 8)
+        if (carlson) return fwd_tile_nb<1, double, Real, kIlCarlson>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
     return fwd_tile_nb<1, double, Real, kIlExact>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
 }
 
 // cylinder launches by I_l variant: area mode 0 exact, 2 trapezoid, 3 tables
 template <class Real>
-hipError_t fwd_sparse_cyl(int mode, int nb, dim3 grid, const KParams& P, const Real* coef, double* f, hipStream_t s)
+hipError_t fwd_sparse_cyl(int mode, bool carlson, int nb, dim3 grid, const KParams& P, const Real* coef, double* f, hipStream_t s)
 {
     if (mode == 2) return fwd_sparse_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, coef, f, s);
     if (mode == 3) return fwd_sparse_nb<1, double, Real, kIlTable>(nb, grid, P, coef, f, s);
+    if constexpr (sizeof(Real) == 8)
+        if (carlson) return fwd_sparse_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
     return fwd_sparse_nb<1, double, Real, kIlExact>(nb, grid, P, coef, f, s);
+}
+
+template <class Real>
+hipError_t fwd_wave_cyl(int mode, bool carlson, int nb, dim3 grid, const KParams& P, const Real* coef, double* f,
+                        hipStream_t s)
+{
+    if (mode == 2) return fwd_wave_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, coef, f, s);
+    if (mode == 3) return fwd_wave_nb<1, double, Real, kIlTable>(nb, grid, P, coef, f, s);
+    if constexpr (sizeof(Real) == 8)
+        if (carlson) return fwd_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
+    return fwd_wave_nb<1, double, Real, kIlExact>(nb, grid, P, coef, f, s);
+}
+
+template <class Real>
+hipError_t adj_wave_cyl(int mode, bool carlson, int nb, dim3 grid, const KParams& P, const Real* W, Real* out,
+                        double* z64, int direct, hipStream_t s)
+{
+    if (mode == 2) return adj_wave_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, W, out, z64, direct, s);
+    if (mode == 3) return adj_wave_nb<1, double, Real, kIlTable>(nb, grid, P, W, out, z64, direct, s);
+    if constexpr (sizeof(Real) == 8)
+        if (carlson) return adj_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, W, out, z64, direct, s);
+    return adj_wave_nb<1, double, Real, kIlExact>(nb, grid, P, W, out, z64, direct, s);
 }
 
 template <class AT, class Real>
@@ -1127,15 +1239,13 @@ hipError_t forward_t(const LaunchPlan& L, const Real* coef, Real* sig, int B, hi
                 e = fwd_tile_nb<0, Real, Real, kIlExact>(nb, P, G.items, G.nitems, L.tile, L.ntiles, L.nbricks, cb,
                                                          fb, s);
             else if (tiles)
-                e = fwd_tile_cyl<Real>(L.mode, nb, P, G.items, G.nitems, L.tile, L.ntiles, L.nbricks, cb, fb, s);
+                e = fwd_tile_cyl<Real>(L.mode, G.carlson, nb, P, G.items, G.nitems, L.tile, L.ntiles, L.nbricks, cb, fb, s);
             else if (sparse && G.shape == 0) e = fwd_sparse_nb<0, Real, Real, kIlExact>(nb, grid, P, cb, fb, s);
-            else if (sparse) e = fwd_sparse_cyl<Real>(L.mode, nb, grid, P, cb, fb, s);
+            else if (sparse) e = fwd_sparse_cyl<Real>(L.mode, G.carlson, nb, grid, P, cb, fb, s);
             else {
                 const dim3 gw((unsigned)L.ncubes, (G.nk + G.kchunk_fwd - 1) / G.kchunk_fwd);
                 if (G.shape == 0) e = fwd_wave_nb<0, Real, Real, kIlExact>(nb, gw, P, cb, fb, s);
-                else if (L.mode == 2) e = fwd_wave_nb<1, double, Real, kIlTrapezoid>(nb, gw, P, cb, fb, s);
-                else if (L.mode == 3) e = fwd_wave_nb<1, double, Real, kIlTable>(nb, gw, P, cb, fb, s);
-                else e = fwd_wave_nb<1, double, Real, kIlExact>(nb, gw, P, cb, fb, s);
+                else e = fwd_wave_cyl<Real>(L.mode, G.carlson, nb, gw, P, cb, fb, s);
             }
             if (e != hipSuccess) return e;
         }
@@ -1179,9 +1289,7 @@ hipError_t adjoint_t(const LaunchPlan& L, const Real* sig, Real* coef, int B, hi
             else {
                 const dim3 gw((unsigned)L.ncubes, (G.nk + G.kchunk_adj - 1) / G.kchunk_adj);
                 if (G.shape == 0) e = adj_wave_nb<0, Real, Real, kIlExact>(nb, gw, P, Wb, ob, zb, direct, s);
-                else if (L.mode == 2) e = adj_wave_nb<1, double, Real, kIlTrapezoid>(nb, gw, P, Wb, ob, zb, direct, s);
-                else if (L.mode == 3) e = adj_wave_nb<1, double, Real, kIlTable>(nb, gw, P, Wb, ob, zb, direct, s);
-                else e = adj_wave_nb<1, double, Real, kIlExact>(nb, gw, P, Wb, ob, zb, direct, s);
+                else e = adj_wave_cyl<Real>(L.mode, G.carlson, nb, gw, P, Wb, ob, zb, direct, s);
             }
             if (e != hipSuccess) return e;
         }

@@ -6,6 +6,26 @@
 
 namespace patop {
 
+#if defined(__clang__)
+typedef __attribute__((address_space(3))) double LdsDouble;
+#else
+typedef double LdsDouble;
+#endif
+
+// frame coordinates of a voxel (Sec. 4.1 / Sec. 4.2 frames), FP64
+__device__ __forceinline__ void frame_coords(const TrDev& T, int ix, int iy, int iz, double x[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) x[a] = fma(T.g[a][0], ix, fma(T.g[a][1], iy, fma(T.g[a][2], iz, T.base[a])));
+}
+
+// the work-group's copy of kArcTable (no barrier here)
+template <int STRIDE>
+__device__ __forceinline__ void load_arc_table(double* tab)
+{
+    for (int i = threadIdx.x; i < kArcTab; i += STRIDE) tab[i] = kArcTable[i];
+}
+
 // ---------------------------------------------------------------------------
 // per-pair geometry: reflected quadrants of the parameter rectangle
 // (Eq. uvminmax; Eq. folded_intervals for the cylinder), built one at a time
@@ -55,7 +75,10 @@ struct PlanarPair {
     WInt U, V;
     double z2;
     const double* tab;
-    __device__ __forceinline__ void bind(double*, const double2*, const double* t) { tab = t; }
+    __device__ __forceinline__ void bind(double*, const double2*, const double* t, const TrDev*, int, int, int)
+    {
+        tab = t;
+    }
     __device__ __forceinline__ void setup(const TrDev& T, const double x[3], double)
     {
         double L1 = T.p[0], L2 = T.p[1];
@@ -120,7 +143,7 @@ struct CylinderPair {
     double* box;             // this thread's column of the LDS box table
     int list, nq;            // non-empty quadrants (2 bits each, in sweep order) and their number
     int wbits;               // quadrant weights: bits 0/1 the U intervals, 2/3 the V intervals (set = 2)
-    __device__ __forceinline__ void bind(double* table, const double2* lut, const double*)
+    __device__ __forceinline__ void bind(double* table, const double2* lut, const double*, const TrDev*, int, int, int)
     {
         box = table + threadIdx.x;
         P.lut = lut;
@@ -225,25 +248,78 @@ struct CylinderPair {
     }
 };
 
+// Whether the weight's polynomials serve a pair, whose u-intervals end at the
+// cosines [c0, c1] and [cm, cp] (where ok), and whether some interval needs the
+// higher degree.  They cover |tau| <= eta of x = w^2 / mu on its side of pi/2.  The
+// recurrence of the J_j loses (vmax^2 / (mu (1 - xc)))^N roundings, so voxels
+// closer to the focal line than that, and within 1e-7 R of it, keep the elliptic
+// integral.  So do, with FP64 input and output, those whose interval reaches u =
+// pi: the integral's end points round there by up to 1e-8 of a bin, and FP64
+// signals stay within 1e-9 of the ones earlier versions returned.
+struct ArcFit {
+    bool fits, wide;
+};
+template <int NW>
+__host__ __device__ inline ArcFit arc_fit(double R, double rho, double c0, double c1, double cm, double cp, bool ok0,
+                                          bool ok1, double vmax, bool inpi)
+{
+    const double mu = 4.0 * R * rho;
+    ArcFit r{mu >= 4e-7 * R * R && !(NW >= 2 && inpi), false};
+    for (int i = 0; i < 2; ++i) {
+        if (!(i ? ok1 : ok0)) continue;
+        const double ca = i ? cm : c0, cb = i ? cp : c1, g = ca + cb > 0.0 ? 0.5 : -0.5;
+        const double xa = fma(-g, ca, 0.5), xb = fma(-g, cb, 0.5);
+        const double one = 1.0 - 0.5 * (xa + xb), del = 0.5 * fabs(xb - xa);
+        r.fits = r.fits && del <= Weight<NW, true>::eta * one && vmax * vmax <= mu * one;
+        r.wide = r.wide || del > Weight<NW, false>::eta * one;
+    }
+    return r;
+}
+
+// One pair by its elliptic integrals, out of line: the few pairs that need it
+// would otherwise cost every other one registers (inlined, the cylinder kernels
+// kept 84 spilled registers instead of 41).  The sink travels by value, with LDS
+// pointers typed as such.
+template <int NW, int STRIDE, class Sink>
+__device__ __attribute__((noinline)) Sink carlson_pair(const TrDev* tr, int ix, int iy, int iz, int wlo, int whi,
+                                                        double r0, LdsDouble* box, Sink sink)
+{
+    const TrDev T = *tr;
+    double x[3];
+    frame_coords(T, ix, iy, iz, x);
+    CylinderPair<NW, kIlExact, STRIDE> pair;
+    pair.box = (double*)box;
+    pair.P.lut = nullptr;
+    pair.setup(T, x, r0);
+    pair.sweep(wlo, whi, sink, r0);
+    return sink;
+}
+
 // Exact I_l: the quadrants as weighted areas (arc_sweep), for a pair whose
 // folded u-intervals the weight's polynomials cover, else Carlson's integral
 // (CylinderPair).  The ends of the intervals are kept as cos and sin, which the
 // frame coordinates give without an inverse function.
 template <int NW, int STRIDE>
 struct ArcCylinderPair {
-    static constexpr int kNarrow = NW == 1 ? 5 : 7, kWide = NW == 1 ? 8 : 10;   // degrees of p
+    using Narrow = Weight<NW, false>;   // degrees of p
+    using Wide = Weight<NW, true>;
     double R, rho;
     double* box;             // this thread's column of the LDS box table
     const double* tab;
     int list, nq;            // non-empty quadrants (2 bits each, in sweep order) and their number
     int bits;                // bit 0 / 1: U / V interval 0 has weight 2; bit 2 / 3: U interval 0 ends at
                              // u = 0 / pi; bit 4: some interval needs the higher degree; bit 5: Carlson
-    CylinderPair<NW, kIlExact, STRIDE> ell;
-    __device__ __forceinline__ void bind(double* table, const double2* lut, const double* t)
+    const TrDev* tr;         // the pair, for Carlson's path
+    int ix, iy, iz;
+    __device__ __forceinline__ void bind(double* table, const double2*, const double* t, const TrDev* T, int x, int y,
+                                         int z)
     {
         box = table + threadIdx.x;
         tab = t;
-        ell.bind(table, lut, t);
+        tr = T;
+        ix = x;
+        iy = y;
+        iz = z;
     }
     // w^2 / mu = sin^2(u/2) from cos u and sin u, without cancellation for small u
     static __device__ __forceinline__ double half_sin2(double c, double s)
@@ -269,27 +345,10 @@ struct ArcCylinderPair {
         const bool uok[2] = {c0 > c1, (in0 || inpi) && cm > cp};
         const double vmax = V.n == 2 ? V.hi[1] : V.hi[0];
         bits = (in0 || inpi ? 1 : 0) | (V.n == 2 ? 2 : 0) | (in0 ? 4 : 0) | (inpi ? 8 : 0);
-        // the weight's argument over each interval, x = w^2 / mu on its side of
-        // pi/2: the polynomials cover |tau| <= eta.  The recurrence of the J_j
-        // loses (vmax^2 / (mu (1 - xc)))^N roundings, so voxels closer to the focal
-        // line than that, and within 1e-7 R of it, keep the elliptic integral.
-        // So do, with FP64 input and output, those whose interval reaches u = pi:
-        // the integral's end points round there by up to 1e-8 of a bin, and FP64
-        // signals stay within 1e-9 of the ones earlier versions returned.
-        const double mu = 4.0 * R * rho;
-        bool fits = mu >= 4e-7 * R * R && !(NW >= 2 && inpi);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if (!uok[i]) continue;
-            const double ca = i ? cm : c0, cb = i ? cp : c1, g = ca + cb > 0.0 ? 0.5 : -0.5;
-            const double xa = fma(-g, ca, 0.5), xb = fma(-g, cb, 0.5);
-            const double one = 1.0 - 0.5 * (xa + xb), del = 0.5 * fabs(xb - xa);
-            fits = fits && del <= Weight<kWide>::eta * one && vmax * vmax <= mu * one;
-            if (del > Weight<kNarrow>::eta * one) bits |= 16;
-        }
-        if (!fits) {
+        const ArcFit fit = arc_fit<NW>(R, rho, c0, c1, cm, cp, uok[0], uok[1], vmax, inpi);
+        if (fit.wide) bits |= 16;
+        if (!fit.fits) {
             bits |= 32;
-            ell.setup(T, x, r0);
             return;
         }
         // the non-empty quadrants in decreasing order of their number of bins
@@ -326,18 +385,19 @@ struct ArcCylinderPair {
         box[4 * STRIDE] = V.lo[0]; box[5 * STRIDE] = V.hi[0]; box[6 * STRIDE] = V.hi[1];
     }
     // p(om) = scale (1 - x)^(-1/2): Weight's polynomial in tau = al om + be, expanded
-    template <int N>
-    static __device__ __forceinline__ void weight(ArcQuad<N>& q, double al, double be, double scale)
+    template <class Wt>
+    static __device__ __forceinline__ void weight(ArcQuad<Wt::n>& q, double al, double be, double scale)
     {
+        constexpr int N = Wt::n;
         double p[N + 1];
 #pragma unroll
         for (int i = 0; i <= N; ++i) p[i] = 0.0;
-        p[0] = Weight<N>::c[N];
+        p[0] = Wt::c[N];
 #pragma unroll
         for (int j = N - 1; j >= 0; --j) {
 #pragma unroll
             for (int i = N - j; i > 0; --i) p[i] = fma(be, p[i], al * p[i - 1]);
-            p[0] = fma(be, p[0], Weight<N>::c[j]);
+            p[0] = fma(be, p[0], Wt::c[j]);
         }
 #pragma unroll
         for (int j = 0; j <= N; ++j) {
@@ -346,10 +406,11 @@ struct ArcCylinderPair {
             q.Q[j] = p[j] * (1.0 / (2 * j + 1));
         }
     }
-    template <int N, int S, class Sink>
+    template <class Wt, int S, class Sink>
     __device__ __forceinline__ void arc(double xN, double xF, double c, double d, double w, double mu, double r0,
                                         int wlo, int whi, Sink& sink) const
     {
+        constexpr int N = Wt::n;
         ArcQuad<N> q;
         const double b = S > 0 ? R - rho : R + rho;
         q.base2 = b * b;
@@ -358,11 +419,11 @@ struct ArcCylinderPair {
         q.wF = sqrt64<NW>(o2); q.oF = S * o2;
         const double xc = 0.5 * (xN + xF), ione = rcp_nw<NW>(1.0 - xc);
         const double smu = rsq64<NW>(mu);   // 1 / sqrt(mu)
-        weight<N>(q, S * ione * (smu * smu), -xc * ione, S * w * 2.0 * R * (smu * sqrt64<NW>(ione)));
+        weight<Wt>(q, S * ione * (smu * smu), -xc * ione, S * w * 2.0 * R * (smu * sqrt64<NW>(ione)));
         arc_finish<N, S>(q, c, d, r0);
         arc_sweep<N, S, NW>(q, r0, wlo, whi, tab, sink);
     }
-    template <int N, class Sink>
+    template <class Wt, class Sink>
     __device__ __forceinline__ void arcs(int wlo, int whi, Sink& sink, double r0) const
     {
         const double mu = 4.0 * R * rho;
@@ -376,9 +437,9 @@ struct ArcCylinderPair {
             const double c = j ? box[5 * STRIDE] : box[4 * STRIDE], d = j ? box[6 * STRIDE] : box[5 * STRIDE];
             const double w = (double)((1 + ((bits & 1) & ~i)) * (1 + (((bits >> 1) & 1) & ~j)));
             if (ca + cb > 0.0)   // the middle of [a, b] is below pi/2
-                arc<N, 1>(half_sin2(ca, sa), half_sin2(cb, sb), c, d, w, mu, r0, wlo, whi, sink);
+                arc<Wt, 1>(half_sin2(ca, sa), half_sin2(cb, sb), c, d, w, mu, r0, wlo, whi, sink);
             else
-                arc<N, -1>(half_sin2(-ca, sa), half_sin2(-cb, sb), c, d, w, mu, r0, wlo, whi, sink);
+                arc<Wt, -1>(half_sin2(-ca, sa), half_sin2(-cb, sb), c, d, w, mu, r0, wlo, whi, sink);
         }
     }
     // bins wlo .. whi of each quadrant reach the sink; each edge is evaluated
@@ -387,11 +448,11 @@ struct ArcCylinderPair {
     __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
     {
         if (bits & 32) {
-            ell.sweep(wlo, whi, sink, r0);
+            sink.take(carlson_pair<NW, STRIDE>(tr, ix, iy, iz, wlo, whi, r0, (LdsDouble*)box, sink.give()));
         } else if (__any(bits & 16)) {   // one degree for the wave: its lanes are neighbouring voxels
-            arcs<kWide>(wlo, whi, sink, r0);
+            arcs<Wide>(wlo, whi, sink, r0);
         } else {
-            arcs<kNarrow>(wlo, whi, sink, r0);
+            arcs<Narrow>(wlo, whi, sink, r0);
         }
     }
 };
@@ -403,7 +464,7 @@ struct ArcCylinderPair {
 template <class Real> struct Newton { static constexpr int value = 2; };
 template <> struct Newton<float> { static constexpr int value = 1; };
 
-// IL: how the cylinder's I_l is evaluated (kIlExact, kIlTrapezoid, kIlTable);
+// IL: how the cylinder's I_l is evaluated (kIlExact, kIlCarlson, kIlTrapezoid, kIlTable);
 // the planar area is exact either way
 template <int SHAPE, class Real, int IL, int STRIDE = kThreads> struct PairOf;
 template <class Real, int IL, int STRIDE> struct PairOf<0, Real, IL, STRIDE> {
@@ -414,6 +475,9 @@ template <class Real, int IL, int STRIDE> struct PairOf<1, Real, IL, STRIDE> {
 };
 template <class Real, int STRIDE> struct PairOf<1, Real, kIlExact, STRIDE> {
     using type = ArcCylinderPair<Newton<Real>::value, STRIDE>;
+};
+template <class Real, int STRIDE> struct PairOf<1, Real, kIlCarlson, STRIDE> {
+    using type = CylinderPair<Newton<Real>::value, kIlExact, STRIDE>;
 };
 
 }  // namespace patop

@@ -8,20 +8,31 @@
 
 using namespace patop;
 
+struct Sink {
+    double* out;
+    int lo;
+    long n;
+    int fetch(int) const { return 0; }
+    void add(int m, double area, int)
+    {
+        out[m - lo] += area;
+        ++n;
+    }
+    void operator()(int m, double area) { add(m, area, 0); }
+    Sink give() const { return *this; }
+    void take(const Sink& s) { n = s.n; }
+};
+
 template <class Pair>
 static long sweep(const TrDev& T, const double* x, double r0, int lo, int hi, double* out)
 {
     static double box[16];
-    long n = 0;
-    auto sink = [&](int m, double area) {
-        out[m - lo] += area;
-        ++n;
-    };
+    Sink sink{out, lo, 0};
     Pair p;
-    p.bind(box, nullptr, kArcTable);
+    p.bind(box, nullptr, kArcTable, &T, 0, 0, 0);
     p.setup(T, x, r0);
     p.sweep(lo, hi, sink, r0);
-    return n;
+    return sink.n;
 }
 
 // areas of the bins lo .. hi of one pair; tr = shape and the three sizes, x the
@@ -33,7 +44,10 @@ extern "C" long pair_areas(const double* tr, const double* x, double r0, int lo,
     TrDev T;
     std::memset(&T, 0, sizeof T);
     T.shape = (int)tr[0];
-    for (int i = 0; i < 3; ++i) T.p[i] = tr[1 + i];
+    for (int i = 0; i < 3; ++i) {
+        T.p[i] = tr[1 + i];
+        T.base[i] = x[i];
+    }
     if (T.shape == 0)
         return kind == 0 ? sweep<PairOf<0, float, kIlExact, 1>::type>(T, x, r0, lo, hi, out)
                          : sweep<PairOf<0, double, kIlExact, 1>::type>(T, x, r0, lo, hi, out);
