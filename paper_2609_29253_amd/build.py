@@ -14,6 +14,9 @@ FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared",
     f"--offload-arch={ARCH}",
     "-munsafe-fp-atomics",
+    # constants stay next to their use (scalar moves) instead of being hoisted out
+    # of every loop of a pair sweep and then kept in spilled registers
+    "-mllvm", "-disable-machine-licm",
     # packed FP32 instructions are kept out of every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
