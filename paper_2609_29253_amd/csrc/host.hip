@@ -157,11 +157,11 @@ void free_dev(pat_ctx* c)
 }
 
 // The share of the cylinders' pairs that the weighted areas serve with FP64 input
-// and output (arc_fit), on 4 x 4 x 4 voxels spread over the grid.  Below 0.4 the
-// kernels that evaluate every pair by Carlson's integral are faster, since waves
-// that hold both kinds of pair step through both (A + A^T on 61 x 47 x 53 voxels x
-// 96 cylinders, where 0.3 are served: 8.7 against 8.45 ms; a scan whose focal
-// lines cross the volume, 0.95 served: 16.5 against 21.9).
+// and output (arc_fit), on 4 x 4 x 4 voxels spread over the grid.  Below 0.2
+// the kernels that evaluate every pair by Carlson's integral are faster, since
+// waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
+// the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
+// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).
 double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& grid)
 {
     int64_t fit = 0;
@@ -395,6 +395,7 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     const int nby = (int)((grid->n[1] + kBrickY - 1) / kBrickY);
     const int nbz = (int)((grid->n[2] + kBrickZ - 1) / kBrickZ);
     const int nbricks = nbx * nby * nbz;
+    const int ncubes = (int)(((grid->n[0] + 3) / 4) * ((grid->n[1] + 3) / 4) * ((grid->n[2] + 3) / 4));
     // Work-groups of a brick's size that a launch is split into at least, by chunks
     // of transducers.  The closed-form forward adds into f with atomics whatever
     // its chunks, and four times as many shorten its last round (128^3 x 256
@@ -502,11 +503,11 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.kchunk_fwd = chunk(target_fwd);
         Gp.kchunk_adj = chunk(target_wg);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
-                     arc_share(T.data(), perm.data() + off, nk, *grid) < 0.4;
+                     arc_share(T.data(), perm.data() + off, nk, *grid) < 0.2;
         off += nk;
     }
     Lp.nbricks = nbricks;
-    Lp.ncubes = (int)(((grid->n[0] + 3) / 4) * ((grid->n[1] + 3) / 4) * ((grid->n[2] + 3) / 4));
+    Lp.ncubes = ncubes;
     Lp.mode = p.area_mode;
     Lp.fp64 = p.precision == PAT_FP64;
     Lp.U = p.U;

@@ -325,7 +325,7 @@ struct Count {
 template <int SHAPE, class AT, int NB, class Real, int IL>
 __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy, int iz, bool valid, int64_t idx,
                                                 int kbeg, int kend, const Real* __restrict__ coef,
-                                                double* __restrict__ f, double* hist, double* box, const double* tab)
+                                                double* __restrict__ f, double* hist, double* box, double* tab)
 {
     constexpr int HE = wave_window_bytes<SHAPE>() / (int)sizeof(double);
     constexpr int HW = HE / NB;          // shells per pass
@@ -338,6 +338,8 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
         nz |= p0[b] != 0.0;
     }
     if (!__any(nz)) return;
+    load_arc_table<kWave>(tab);   // after the cubes without a coefficient have left
+    wave_lds_order();
     const int S = P.step;
     const int64_t Mhi = P.Mlo + P.Mcount - 1;
     for (int kk = kbeg; kk < kend; ++kk) {
@@ -404,8 +406,6 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
     const bool valid = ix < P.n[0] && iy < P.n[1] && iz < P.n[2];
     const int64_t idx = valid ? ix + P.n[0] * (iy + P.n[1] * (int64_t)iz) : 0;
     const int kbeg = blockIdx.y * P.kchunk;
-    load_arc_table<kWave>(tab);
-    wave_lds_order();
     fwd_wave_voxels<SHAPE, AT, NB, Real, IL>(P, ix, iy, iz, valid, idx, kbeg, min(P.nk, kbeg + P.kchunk), coef, f,
                                              hist, box, tab);
 }
@@ -423,8 +423,6 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
     __shared__ double hist[wave_window_bytes<SHAPE>() / sizeof(double)];   // [NB][shells per pass]
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
     __shared__ double tab[kArcTab];
-    load_arc_table<kWave>(tab);
-    wave_lds_order();
     const int64_t total = *P.sup_total;
     const int64_t nchunks = (P.nk + P.kchunk - 1) / P.kchunk;
     const int64_t items = (total + kWave - 1) / kWave * nchunks;
@@ -1095,12 +1093,17 @@ __global__ void k_fir_wide(const double* __restrict__ f, const double* __restric
     out[((int64_t)b * K + k) * L + l] = (Real)acc;
 }
 
-// W[b][k][m] = scale[m] sum_l G[U l - m] y[b][k][l]
+// W[b][k][m] = scale[m] sum_l G[U l - m] y[b][k][l]; and z64 <- 0 (nz of them) for the sums
+// that follow, in the same launch
 template <class Real>
 __global__ void k_adjw(const Real* __restrict__ y, const double* __restrict__ scale, const double* __restrict__ G,
-                       int jlo, int jcnt, int U, int L, int K, int64_t Mlo, int64_t Mcount, Real* __restrict__ W)
+                       int jlo, int jcnt, int U, int L, int K, int64_t Mlo, int64_t Mcount, Real* __restrict__ W,
+                       double* __restrict__ z64, int64_t nz)
 {
     const int64_t mi = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * gridDim.y * gridDim.z * blockDim.x;
+    for (int64_t i = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x * blockDim.x + mi; i < nz; i += stride)
+        z64[i] = 0.0;
     const int k = blockIdx.y, b = blockIdx.z;
     if (mi >= Mcount) return;
     const int m = (int)(Mlo + mi);
@@ -1348,16 +1351,12 @@ hipError_t adjoint_t(const LaunchPlan& L, const Real* sig, Real* coef, int B, hi
 {
     hipError_t e;
     Real* W = (Real*)L.W;
-    dim3 g1((unsigned)((L.base.Mcount + 255) / 256), L.base.K, B);
-    k_adjw<Real><<<g1, 256, 0, s>>>(sig, L.scale, L.G, L.jlo, L.jcnt, L.U, L.L, L.base.K,
-                                    L.base.Mlo, L.base.Mcount, W);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bool direct = L.ngroups == 1 && L.groups[0].kchunk_adj >= L.groups[0].nk;
+    const bool direct = L.ngroups == 1 && L.groups[0].kchunk_adj >= L.groups[0].nk;
     const int64_t nz = (int64_t)B * L.base.N;
-    if (!direct) {
-        k_fill<<<grid_fill_blocks(nz), 256, 0, s>>>(L.z64, nz);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
+    dim3 g1((unsigned)((L.base.Mcount + 255) / 256), L.base.K, B);
+    k_adjw<Real><<<g1, 256, 0, s>>>(sig, L.scale, L.G, L.jlo, L.jcnt, L.U, L.L, L.base.K, L.base.Mlo, L.base.Mcount,
+                                    W, L.z64, direct ? 0 : nz);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int b0 = 0; b0 < B;) {
         const int nb = chunk_nb(B - b0);
         for (int g = 0; g < L.ngroups; ++g) {
