@@ -171,34 +171,49 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 // along v = c until the corner (F, c) and is then clamped at the far end F.
 
 // h's factor (1 - x)^(-1/2) = (1 - xc)^(-1/2) (1 - tau)^(-1/2), tau = (x - xc) /
-// (1 - xc): interpolant of degree N at Chebyshev nodes on |tau| <= eta, of relative
-// error 1.6e-9 (N = 4) and 7.5e-10 (7) for FP32 input and output, whose signals
-// round at 6e-8 and to which these errors pass undivided (each bin's area changes
-// by that share), and 6.2e-14 (7) and 3.3e-13 (10) for FP64.
-template <int NW, bool WIDE> struct Weight;
-template <> struct Weight<1, false> {
+// (1 - xc): interpolants of degree n at Chebyshev nodes on |tau| <= eta, by level.
+// Relative error with FP32 input and output 1.6e-9, 1.9e-9 and 7.5e-10: their signals
+// round at 6e-8, and these errors pass to them undivided (each bin's area changes
+// by that share); with FP64 6.2e-14, 1.0e-13 and 3.3e-13.  kappa bounds vmax^2 / (mu
+// (1 - xc)), whose n-th power multiplies the roundings of the J_j.
+template <int NW, int LEVEL> struct Weight;
+template <> struct Weight<1, 0> {
     static constexpr int n = 4;
-    static constexpr double eta = 0.04;
+    static constexpr double eta = 0.04, kappa = 3.2;
     static constexpr double c[n + 1] = {
         1.0, 0.4999998027893683, 0.3749998192165893, 0.31299285870394444, 0.2738893011398508};
 };
-template <> struct Weight<1, true> {
+template <> struct Weight<1, 1> {
+    static constexpr int n = 5;
+    static constexpr double eta = 0.08, kappa = 2.6;
+    static constexpr double c[n + 1] = {
+        1.0000000018635444, 0.5000000017306818, 0.3749947604041674, 0.31249513399010315, 0.2756167786712076,
+        0.24811758344361434};
+};
+template <> struct Weight<1, 2> {
     static constexpr int n = 7;
-    static constexpr double eta = 0.16;
+    static constexpr double eta = 0.16, kappa = 2.0;
     static constexpr double c[n + 1] = {
         0.9999999993097828, 0.49999999934780515, 0.375000862151671, 0.31250081465170293, 0.27326976417167687,
         0.24593526203177093, 0.23596719691165274, 0.21928054205212558};
 };
-template <> struct Weight<2, false> {
+template <> struct Weight<2, 0> {
     static constexpr int n = 7;
-    static constexpr double eta = 0.05;
+    static constexpr double eta = 0.05, kappa = 1.3;
     static constexpr double c[n + 1] = {
         0.9999999999999398, 0.49999999999994316, 0.37500000077050993, 0.31250000072773826, 0.27343595956342226,
         0.24609229508034408, 0.2265708771687404, 0.21040290777839668};
 };
-template <> struct Weight<2, true> {
+template <> struct Weight<2, 1> {
+    static constexpr int n = 8;
+    static constexpr double eta = 0.08, kappa = 1.2;
+    static constexpr double c[n + 1] = {
+        1.0, 0.49999999998891637, 0.37499999998946937, 0.3125000230808288, 0.27343752192922083,
+        0.24608078231340225, 0.22557361695740225, 0.21216685744128233, 0.19894030261705037};
+};
+template <> struct Weight<2, 2> {
     static constexpr int n = 10;
-    static constexpr double eta = 0.16;
+    static constexpr double eta = 0.16, kappa = 1.0;
     static constexpr double c[n + 1] = {
         1.0, 0.5000000000212094, 0.3750000000203339, 0.31249998344974184, 0.2734374841330066,
         0.2460973593854478, 0.2255893978103804, 0.20915235533051377, 0.19607355491324047, 0.1978170102153056,

@@ -161,7 +161,9 @@ void free_dev(pat_ctx* c)
 // the kernels that evaluate every pair by Carlson's integral are faster, since
 // waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
 // the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
-// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).
+// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).  A launch of
+// few waves lasts as long as its slowest one, so there the line is at 0.8 (16^3 x
+// 64 elements of a scan, A^T: 92 against 95 us).
 double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& grid)
 {
     int64_t fit = 0;
@@ -179,7 +181,7 @@ double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& gri
             const bool in0 = sm < 0.0, inpi = !in0 && sp < 0.0;
             fit += arc_fit<2>(t.p[0], rho, in0 ? 1.0 : inpi ? cp : cm, in0 ? cm : inpi ? -1.0 : cp, cm, cp, true, in0 || inpi,
                               std::fabs(x[2]) + t.p[2], inpi)
-                       .fits;
+                       .fits();
         }
     }
     return (double)fit / (64.0 * n);
@@ -503,7 +505,8 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.kchunk_fwd = chunk(target_fwd);
         Gp.kchunk_adj = chunk(target_wg);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
-                     arc_share(T.data(), perm.data() + off, nk, *grid) < 0.2;
+                     arc_share(T.data(), perm.data() + off, nk, *grid) <
+                         ((int64_t)ncubes * nk < 8192 ? 0.8 : 0.2);
         off += nk;
     }
     Lp.nbricks = nbricks;

@@ -248,30 +248,36 @@ struct CylinderPair {
     }
 };
 
-// Whether the weight's polynomials serve a pair, whose u-intervals end at the
-// cosines [c0, c1] and [cm, cp] (where ok), and whether some interval needs the
-// higher degree.  They cover |tau| <= eta of x = w^2 / mu on its side of pi/2.  The
-// recurrence of the J_j loses (vmax^2 / (mu (1 - xc)))^N roundings, so voxels
-// closer to the focal line than that, and within 1e-7 R of it, keep the elliptic
-// integral.  So do, with FP64 input and output, those whose interval reaches u =
-// pi: the integral's end points round there by up to 1e-8 of a bin, and FP64
-// signals stay within 1e-9 of the ones earlier versions returned.
+// Which levels of the weight's polynomials serve a pair, whose u-intervals end at the
+// cosines [c0, c1] and [cm, cp] (where ok): least <= level <= most (most = -1: none).
+// They cover |tau| <= eta of x = w^2 / mu on its side of pi/2.  The recurrence of the
+// J_j loses (vmax^2 / (mu (1 - xc)))^n roundings, so voxels closer to the focal line
+// than kappa, and within 1e-7 R of it, keep the elliptic integral.  So do, with FP64
+// input and output, those whose interval reaches u = pi: the integral's end points
+// round there by up to 1e-8 of a bin, and FP64 signals stay within 1e-9 of the ones
+// earlier versions returned.
 struct ArcFit {
-    bool fits, wide;
+    int least, most;
+    __host__ __device__ bool fits() const { return least <= most; }
 };
 template <int NW>
 __host__ __device__ inline ArcFit arc_fit(double R, double rho, double c0, double c1, double cm, double cp, bool ok0,
                                           bool ok1, double vmax, bool inpi)
 {
-    const double mu = 4.0 * R * rho;
-    ArcFit r{mu >= 4e-7 * R * R && !(NW >= 2 && inpi), false};
+    using W0 = Weight<NW, 0>;
+    using W1 = Weight<NW, 1>;
+    using W2 = Weight<NW, 2>;
+    const double mu = 4.0 * R * rho, v2 = vmax * vmax;
+    ArcFit r{0, mu >= 4e-7 * R * R && !(NW >= 2 && inpi) ? 2 : -1};
     for (int i = 0; i < 2; ++i) {
         if (!(i ? ok1 : ok0)) continue;
         const double ca = i ? cm : c0, cb = i ? cp : c1, g = ca + cb > 0.0 ? 0.5 : -0.5;
         const double xa = fma(-g, ca, 0.5), xb = fma(-g, cb, 0.5);
-        const double one = 1.0 - 0.5 * (xa + xb), del = 0.5 * fabs(xb - xa);
-        r.fits = r.fits && del <= Weight<NW, true>::eta * one && vmax * vmax <= mu * one;
-        r.wide = r.wide || del > Weight<NW, false>::eta * one;
+        const double one = 1.0 - 0.5 * (xa + xb), del = 0.5 * fabs(xb - xa), m1 = mu * one;
+        const int least = del <= W0::eta * one ? 0 : del <= W1::eta * one ? 1 : del <= W2::eta * one ? 2 : 3;
+        const int most = v2 <= W2::kappa * m1 ? 2 : v2 <= W1::kappa * m1 ? 1 : v2 <= W0::kappa * m1 ? 0 : -1;
+        r.least = r.least > least ? r.least : least;
+        r.most = r.most < most ? r.most : most;
     }
     return r;
 }
@@ -301,14 +307,13 @@ __device__ __attribute__((noinline)) Sink carlson_pair(const TrDev* tr, int ix, 
 // frame coordinates give without an inverse function.
 template <int NW, int STRIDE>
 struct ArcCylinderPair {
-    using Narrow = Weight<NW, false>;   // degrees of p
-    using Wide = Weight<NW, true>;
     double R, rho;
     double* box;             // this thread's column of the LDS box table
     const double* tab;
     int list, nq;            // non-empty quadrants (2 bits each, in sweep order) and their number
     int bits;                // bit 0 / 1: U / V interval 0 has weight 2; bit 2 / 3: U interval 0 ends at
-                             // u = 0 / pi; bit 4: some interval needs the higher degree; bit 5: Carlson
+                             // u = 0 / pi; bits 4 / 5: the weight's level is at least 1 / 2; bits 6-8:
+                             // level 0 / 1 / 2 does not serve, all of them for Carlson's path
     const TrDev* tr;         // the pair, for Carlson's path
     int ix, iy, iz;
     __device__ __forceinline__ void bind(double* table, const double2*, const double* t, const TrDev* T, int x, int y,
@@ -346,9 +351,8 @@ struct ArcCylinderPair {
         const double vmax = V.n == 2 ? V.hi[1] : V.hi[0];
         bits = (in0 || inpi ? 1 : 0) | (V.n == 2 ? 2 : 0) | (in0 ? 4 : 0) | (inpi ? 8 : 0);
         const ArcFit fit = arc_fit<NW>(R, rho, c0, c1, cm, cp, uok[0], uok[1], vmax, inpi);
-        if (fit.wide) bits |= 16;
-        if (!fit.fits) {
-            bits |= 32;
+        if (!fit.fits()) {
+            bits |= 7 << 6;
             return;
         }
         // the non-empty quadrants in decreasing order of their number of bins
@@ -380,6 +384,7 @@ struct ArcCylinderPair {
                 rank += (qj != qi) && (len[qj] > len[qi] || (len[qj] == len[qi] && qj < qi));
             if (ok[qi]) { list |= qi << (2 * rank); ++nq; }
         }
+        bits |= (fit.least << 4) | ((6 << fit.most) & 6) << 6;
         box[0 * STRIDE] = cm; box[1 * STRIDE] = fabs(sm);
         box[2 * STRIDE] = cp; box[3 * STRIDE] = fabs(sp);
         box[4 * STRIDE] = V.lo[0]; box[5 * STRIDE] = V.hi[0]; box[6 * STRIDE] = V.hi[1];
@@ -444,16 +449,25 @@ struct ArcCylinderPair {
     }
     // bins wlo .. whi of each quadrant reach the sink; each edge is evaluated
     // on its own, so the walk starts at max(mfirst, wlo)
+    template <int LEVEL, class Sink>
+    __device__ __forceinline__ void arcs_or_carlson(int wlo, int whi, Sink& sink, double r0)
+    {
+        if (bits & (64 << LEVEL))
+            sink.take(carlson_pair<NW, STRIDE>(tr, ix, iy, iz, wlo, whi, r0, (LdsDouble*)box, sink.give()));
+        else
+            arcs<Weight<NW, LEVEL>>(wlo, whi, sink, r0);
+    }
     template <class Sink>
     __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
     {
-        if (bits & 32) {
-            sink.take(carlson_pair<NW, STRIDE>(tr, ix, iy, iz, wlo, whi, r0, (LdsDouble*)box, sink.give()));
-        } else if (__any(bits & 16)) {   // one degree for the wave: its lanes are neighbouring voxels
-            arcs<Wide>(wlo, whi, sink, r0);
-        } else {
-            arcs<Narrow>(wlo, whi, sink, r0);
-        }
+        // one level for the wave's lanes, which are neighbouring voxels; a lane it
+        // does not serve takes Carlson's path
+        if (__any(bits & 32))
+            arcs_or_carlson<2>(wlo, whi, sink, r0);
+        else if (__any(bits & 16))
+            arcs_or_carlson<1>(wlo, whi, sink, r0);
+        else
+            arcs_or_carlson<0>(wlo, whi, sink, r0);
     }
 };
 
