@@ -162,8 +162,11 @@ void free_dev(pat_ctx* c)
 // waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
 // the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
 // 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).  A launch of
-// few waves lasts as long as its slowest one, so there the line is at 0.8 (16^3 x
-// 64 elements of a scan, A^T: 92 against 95 us).
+// few waves lasts as long as its slowest ones, which hold both kinds, so below 24576
+// every sampled pair has to be served (elements of a scan, A / A^T, Carlson against
+// mixed: 22 x 14 x 22 x 26, 3744 waves, 46 / 46 against 67 / 67 us; 28^3 x 64, 21952
+// waves, 195 / 215 against 210 / 243 us; 32^3 x 64, 32768 waves, 339 / 354 against
+// 324 / 337 us; 80^3 x 64 6.9 / 7.5 against 4.7 / 5.1 ms).
 double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& grid)
 {
     int64_t fit = 0;
@@ -506,7 +509,7 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.kchunk_adj = chunk(target_wg);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
                      arc_share(T.data(), perm.data() + off, nk, *grid) <
-                         ((int64_t)ncubes * nk < 8192 ? 0.8 : 0.2);
+                         ((int64_t)ncubes * nk < 24576 ? 1.0 : 0.2);
         off += nk;
     }
     Lp.nbricks = nbricks;
