@@ -317,6 +317,21 @@ struct Count {
     __device__ __forceinline__ void take(const Count& s) { n = s.n; }
 };
 
+// First voxel of a one-wave work-group's cube.  Work-groups go to the 32 shader
+// engines in turn, and an engine without a free slot holds up the others: where
+// 32 divides the cubes of a row, each engine would see the same columns of the
+// volume in every row, and the costliest column would set the pace (128^3 x 256
+// cylinders: 2.5 waves per SIMD resident of 4 possible).  So each row starts at
+// a column of its own.
+__device__ __forceinline__ void wave_cube(const KParams& P, int& x0, int& y0, int& z0)
+{
+    const unsigned ncx = (P.n[0] + 3) / 4, ncy = (P.n[1] + 3) / 4;
+    const unsigned row = blockIdx.x / ncx, start = ((row + 1) * 0x9e3779b9u) >> 16;
+    x0 = (int)((blockIdx.x - row * ncx + start) % ncx) * 4;
+    y0 = (int)(row % ncy) * 4;
+    z0 = (int)(row / ncy) * 4;
+}
+
 // The wave's 64 voxels (one per lane; `valid` false for lanes without one)
 // against transducers kperm[kbeg .. kend): per transducer the window is the
 // union of the lanes' pair ranges, swept in passes of HW shells.  The wave owns
@@ -398,9 +413,8 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_fwd_
     __shared__ double hist[wave_window_bytes<SHAPE>() / sizeof(double)];   // [NB][shells per pass]
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
     __shared__ double tab[kArcTab];
-    const int ncx = (int)((P.n[0] + 3) / 4), ncy = (int)((P.n[1] + 3) / 4);
-    const int cid = blockIdx.x;
-    const int x0 = (cid % ncx) * 4, y0 = ((cid / ncx) % ncy) * 4, z0 = (cid / (ncx * ncy)) * 4;
+    int x0, y0, z0;
+    wave_cube(P, x0, y0, z0);
     const int l = threadIdx.x;
     const int ix = x0 + (l & 3), iy = y0 + ((l >> 2) & 3), iz = z0 + (l >> 4);
     const bool valid = ix < P.n[0] && iy < P.n[1] && iz < P.n[2];
@@ -572,9 +586,8 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
     constexpr int HB = HE / NB;          // shells per pass
     __shared__ double box[SHAPE == 1 ? kBoxSlots * kWave : 1];
     __shared__ double tab[kArcTab];
-    const int ncx = (int)((P.n[0] + 3) / 4), ncy = (int)((P.n[1] + 3) / 4);
-    const int cid = blockIdx.x;
-    const int x0 = (cid % ncx) * 4, y0 = ((cid / ncx) % ncy) * 4, z0 = (cid / (ncx * ncy)) * 4;
+    int x0, y0, z0;
+    wave_cube(P, x0, y0, z0);
     const int l = threadIdx.x;
     const int ix = x0 + (l & 3), iy = y0 + ((l >> 2) & 3), iz = z0 + (l >> 4);
     const bool valid = ix < P.n[0] && iy < P.n[1] && iz < P.n[2];
