@@ -82,6 +82,17 @@ __device__ __forceinline__ void brick_box(const KParams& P, int bid, double lo[3
     lo[2] = P.origin[2] + z0 * P.w; hi[2] = P.origin[2] + z1 * P.w;
 }
 
+// Column of a work-group's cube or brick in its row of nx.  Work-groups go to the 32 shader
+// engines in turn, and an engine without a free slot holds up the others: where
+// 32 divides nx, each engine would see the same columns of the volume in every
+// row, and the costliest would set the pace (128^3 x 256 cylinders: 2.5 waves per
+// SIMD resident of 4 possible, and 3.96 with each row starting at a column of its
+// own: A 69.3 -> 64.1 ms, A^T 80.8 -> 68.2; 256^3 x 512 rectangles A 275 -> 263).
+__device__ __forceinline__ unsigned spread_column(unsigned id, unsigned row, unsigned nx)
+{
+    return (id - row * nx + (((row + 1) * 0x9e3779b9u) >> 16)) % nx;
+}
+
 __device__ __forceinline__ void brick_setup(const KParams& P, int bid, Brick& Bk)
 {
     const int bxi = bid % P.nbx, byi = (bid / P.nbx) % P.nby, bzi = bid / (P.nbx * P.nby);
@@ -317,17 +328,11 @@ struct Count {
     __device__ __forceinline__ void take(const Count& s) { n = s.n; }
 };
 
-// First voxel of a one-wave work-group's cube.  Work-groups go to the 32 shader
-// engines in turn, and an engine without a free slot holds up the others: where
-// 32 divides the cubes of a row, each engine would see the same columns of the
-// volume in every row, and the costliest column would set the pace (128^3 x 256
-// cylinders: 2.5 waves per SIMD resident of 4 possible).  So each row starts at
-// a column of its own.
+// First voxel of a one-wave work-group's cube
 __device__ __forceinline__ void wave_cube(const KParams& P, int& x0, int& y0, int& z0)
 {
-    const unsigned ncx = (P.n[0] + 3) / 4, ncy = (P.n[1] + 3) / 4;
-    const unsigned row = blockIdx.x / ncx, start = ((row + 1) * 0x9e3779b9u) >> 16;
-    x0 = (int)((blockIdx.x - row * ncx + start) % ncx) * 4;
+    const unsigned ncx = (P.n[0] + 3) / 4, ncy = (P.n[1] + 3) / 4, row = blockIdx.x / ncx;
+    x0 = (int)spread_column(blockIdx.x, row, ncx) * 4;
     y0 = (int)(row % ncy) * 4;
     z0 = (int)(row / ncy) * 4;
 }
@@ -743,7 +748,8 @@ __global__ __launch_bounds__(kThreads) void k_fwd_quad(KParams P, const Real* __
     constexpr int HB = kHistQuad;   // bins per pass
     extern __shared__ double hist[];
     Brick Bk;
-    brick_setup(P, blockIdx.x, Bk);
+    const unsigned row = blockIdx.x / (unsigned)P.nbx;
+    brick_setup(P, (int)(row * P.nbx + spread_column(blockIdx.x, row, P.nbx)), Bk);
     double p0[NB];
     bool nz = false;
 #pragma unroll
@@ -830,7 +836,8 @@ __global__ __launch_bounds__(kThreads) void k_adj_quad(KParams P, const Real* __
     extern __shared__ double smem_d[];
     Real* Ws = reinterpret_cast<Real*>(smem_d);
     Brick Bk;
-    brick_setup(P, blockIdx.x, Bk);
+    const unsigned row = blockIdx.x / (unsigned)P.nbx;
+    brick_setup(P, (int)(row * P.nbx + spread_column(blockIdx.x, row, P.nbx)), Bk);
     double acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = 0.0;
