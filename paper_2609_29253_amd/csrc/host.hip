@@ -403,9 +403,14 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     const int ncubes = (int)(((grid->n[0] + 3) / 4) * ((grid->n[1] + 3) / 4) * ((grid->n[2] + 3) / 4));
     // Work-groups of a brick's size that a launch is split into at least, by chunks
     // of transducers.  The closed-form forward adds into f with atomics whatever
-    // its chunks, and four times as many shorten its last round (128^3 x 256
-    // cylinders 77.8 -> 75.2 ms); the adjoint stays in one chunk where it can, so that each voxel's sum has one order.
-    const int target_wg = 4096, target_fwd = surface ? 16384 : target_wg;
+    // its chunks, and eight times as many shorten its last round (128^3 x 256
+    // cylinders 62.4 ms with four times, 61.2 with eight, 61.0 with sixteen).  The
+    // adjoint's sum over a voxel's transducers has one order where at most two terms
+    // are added to the zero that it starts from: two chunks where one work-group
+    // could see every transducer but the waves are few (128^3 x 256 cylinders 67.3 ->
+    // 64.4 ms, 8 x 128^3 x 256 rectangles 14.7 -> 14.0: half the last round); not
+    // with both shapes, whose sums would have four.
+    const int target_wg = 4096, target_fwd = surface ? 32768 : target_wg;
 
     // ---- device allocations
     const size_t rs = p.precision == PAT_FP64 ? sizeof(double) : sizeof(float);
@@ -507,6 +512,8 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         };
         Gp.kchunk_fwd = chunk(target_fwd);
         Gp.kchunk_adj = chunk(target_wg);
+        if (surface && nbricks < 16384 && (nplan == 0 || ncyl == 0))
+            Gp.kchunk_adj = std::min(Gp.kchunk_adj, (nk + 1) / 2);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
                      arc_share(T.data(), perm.data() + off, nk, *grid) <
                          ((int64_t)ncubes * nk < 24576 ? 1.0 : 0.2);
