@@ -566,7 +566,7 @@ def main():
     dom_ms = main_res["ms_forward"]
     dom_name = "k_fwd_wave"
     dom_full = f"k_fwd_wave<{shape}, {'double' if shape == 1 else 'float'}, {min(B, 8) if B > 1 else 1}, float, 0>"
-    area_dtype = "f64" if shape == 1 else "f32"
+    area_dtype = "f64"   # both shapes: areas are FP64 differences
     evals = main_res["evals_per_volume"] * B
     fl = counter_flops(dom_full, prob.name)
     roofline = {"bound": "alu", "achieved": None, "peak": None, "unit": "TFLOP/s", "frac": None,

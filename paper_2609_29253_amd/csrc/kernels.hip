@@ -28,8 +28,8 @@
 //                        staged in LDS, every voxel gathers sum_m |M_i^m| W[m]
 //                        (FP32 or FP64 per transducer) and accumulates over
 //                        transducers in FP64.
-//   3. k_finish          cast of the FP64 sums when transducer chunks were split
-//                        over work-groups.
+//   3. k_finish          cast of the FP64 sums (cleared by k_adjw) when transducer
+//                        chunks were split over work-groups.
 #include <hip/hip_runtime.h>
 
 #include "area.h"
@@ -209,10 +209,10 @@ constexpr int kSparseGrid = 4096;
 
 // Waves per SIMD the closed-form kernels are built for (one-wave work-groups in
 // the dense and sparse forward and the adjoint, 256-thread ones in the time
-// tiles).  The planar kernels hold 107-127 VGPRs without spills and run at four,
-// except FP64 with eight volumes (142).  Cylinders for one or two volumes: four,
-// in 128 VGPRs with spills outside the loops over edges; with more volumes the
-// spills grow and they keep three.
+// tiles).  The planar kernels hold 96-128 VGPRs without spills (five waves at 96),
+// except FP64 with eight volumes (149 in the adjoint: three).  Cylinders for one or
+// two volumes: four, in 128 VGPRs with spills outside the loops over edges; with
+// more volumes the spills grow and they keep three.
 template <int SHAPE, class AT, int NB>
 constexpr int closed_waves()
 {

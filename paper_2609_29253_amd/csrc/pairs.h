@@ -283,8 +283,8 @@ __host__ __device__ inline ArcFit arc_fit(double R, double rho, double c0, doubl
 }
 
 // One pair by its elliptic integrals, out of line: the few pairs that need it
-// would otherwise cost every other one registers (inlined, the cylinder kernels
-// kept 84 spilled registers instead of 41).  The sink travels by value, with LDS
+// would otherwise cost every other one registers (inlined, 84 were spilled; now
+// 18 to 30, outside the loops over edges).  The sink travels by value, with LDS
 // pointers typed as such.
 template <int NW, int STRIDE, class Sink>
 __device__ __attribute__((noinline)) Sink carlson_pair(const TrDev* tr, int ix, int iy, int iz, int wlo, int whi,
