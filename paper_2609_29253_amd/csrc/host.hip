@@ -402,15 +402,16 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     const int nbricks = nbx * nby * nbz;
     const int ncubes = (int)(((grid->n[0] + 3) / 4) * ((grid->n[1] + 3) / 4) * ((grid->n[2] + 3) / 4));
     // Work-groups of a brick's size that a launch is split into at least, by chunks
-    // of transducers.  The closed-form forward adds into f with atomics whatever
-    // its chunks, and eight times as many shorten its last round (128^3 x 256
-    // cylinders 62.4 ms with four times, 61.2 with eight, 61.0 with sixteen).  The
+    // of transducers.  The forward adds into f with atomics whatever its chunks, and
+    // eight times as many as the adjoint's shorten its last round (128^3 x 256 cylinders
+    // 62.4 ms with four times, 61.2 with eight, 61.0 with sixteen; quadrature on 64^3 x 64
+    // 2.83 ms with one, 2.56 with four or eight, on 128^3 x 64 24.9, 24.3 and 24.0).  The
     // adjoint's sum over a voxel's transducers has one order where at most two terms
     // are added to the zero that it starts from: two chunks where one work-group
     // could see every transducer but the waves are few (128^3 x 256 cylinders 67.3 ->
-    // 64.4 ms, 8 x 128^3 x 256 rectangles 14.7 -> 14.0: half the last round); not
-    // with both shapes, whose sums would have four.
-    const int target_wg = 4096, target_fwd = surface ? 32768 : target_wg;
+    // 64.4 ms, 8 x 128^3 x 256 rectangles 14.7 -> 14.0, quadrature on 128^3 x 64 15.2 ->
+    // 14.7: half the last round); not with both shapes, whose sums would have four.
+    const int target_wg = 4096, target_fwd = 32768;
 
     // ---- device allocations
     const size_t rs = p.precision == PAT_FP64 ? sizeof(double) : sizeof(float);
@@ -512,7 +513,7 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         };
         Gp.kchunk_fwd = chunk(target_fwd);
         Gp.kchunk_adj = chunk(target_wg);
-        if (surface && nbricks < 16384 && (nplan == 0 || ncyl == 0))
+        if (nbricks < 16384 && (nplan == 0 || ncyl == 0))
             Gp.kchunk_adj = std::min(Gp.kchunk_adj, (nk + 1) / 2);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
                      arc_share(T.data(), perm.data() + off, nk, *grid) <
