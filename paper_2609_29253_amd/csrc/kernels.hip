@@ -738,7 +738,8 @@ __device__ __forceinline__ void quad_points(double row2, double pc, const ConstD
 // for bin and weight, and the sink's.  Before, each point took six FP64
 // operations from its global coordinates and two FP64 comparisons of its bin.
 // 128^3 voxels x 256 cylinders x 16 x 16 points, FP32: A 141 -> 108 ms, A^T 103 ->
-// 63 ms; FP64: 159 -> 127, 140 -> 106; the same bins and weights bit for bit.  The
+// 63 ms; FP64: 159 -> 127, 140 -> 106; the same bins and weights bit for bit (97 and 60,
+// 120 and 104 ms with the order and number of work-groups as they are now).  The
 // forward is left with its runs: in nearly every step some lane's run ends and
 // the wave steps through the flush.
 template <class AT, int NB, class Real>
