@@ -444,27 +444,148 @@ __device__ __forceinline__ double arc_edge(const ArcQuad<N>& q, double r, const 
     }
 }
 
+// ---------------------------------------------------------------------------
+// rectangles with FP64 input and output
+// ---------------------------------------------------------------------------
+// The area function above is of the size of K = r^2 - |x3|^2, and away from the
+// element's axis K is the square of thousands of bins where a bin's area is a few:
+// its differences keep 2^-53 K.  Here everything is counted from the quadrant's
+// nearest corner (a, c) at distance D: t = r - D, q = r^2 - D^2 = t (t + 2 D), the
+// end points' offsets from the corner as quotients of q and of its differences
+// with E = d^2 - c^2 and F = b^2 - a^2, and the area nearer than r as
+//   pa (d - c) + (pb - pa)(va + vb) / 2 + K (atan x - x / (1 + x^2)):
+// the strip beside the arc, the trapezoid under its chord, and the segment between
+// chord and arc, x = tan(Lambda / 2) = ((pb - pa) + (va - vb)) / (wa + wb + ya + yb).
+// t > 0 from the first edge on, so no edge can fall on the corner or inside it.
+//
+// Two quotients more than arc_edge<0>: A^T of 32^3 x 64 rectangles in FP64 66.8 us
+// against 58.4 (427 by the walk of pieces between corners that both replace).
+// Errors of the worst bin against 40 digits, of the pair's largest bin, medians of this
+// form, of arc_edge<0> and of the walk: 0.5 x 3 mm at 50 MHz, 20 to 60 mm away on
+// the axis 4e-15, 2e-14, 1e-13; 30 degrees off it 1.6e-14, 3e-13, 3e-14; 85 degrees 1.8e-14,
+// 2.6e-12, 1.6e-14; the same at U = 11, 60 degrees 1e-13, 1.1e-11, 1.7e-14 (the area nearer
+// than the edge is 1000 bins there); 0.2 mm at U = 11, 60 degrees 5e-14, 3.5e-11, 7e-14;
+// 0.1 mm at U = 61, 60 degrees 2.6e-13, 2.9e-10, 3.5e-13.
+struct PlaneQuad {
+    double pos, D2, a, c, a2, c2, E, F, G, H;   // D - r0, 2 D, the near corner and its squares, d^2 - c^2,
+                                                // b^2 - a^2, b - a, d - c
+    double w;                                   // weight of the quadrant
+    double S0, S1;
+    int mfirst, mlast;
+};
+
+// (atan x - x / (1 + x^2)) / x^3 by interpolation at Chebyshev nodes of x^2, on x <= 1/8
+// and on x <= 0.42; relative error 4e-17 and 6e-17
+static constexpr double kSegmentLo[7] = {
+    0.6666666666666666, -0.7999999999998448, 0.8571428569838612, -0.8888888277343502,
+    0.9090796942525528, -0.922018712775229, 0.8835386887333297};
+static constexpr double kSegmentHi[12] = {
+    0.6666666666666666, -0.7999999999999372, 0.857142857125834, -0.8888888870770899,
+    0.9090908091655334, -0.9230736588703263, 0.933265379587792, -0.9402379872042317,
+    0.9386152534074689, -0.8972906398300687, 0.7271671936388654, -0.3539903641493709};
+
+template <int M>
+__device__ __forceinline__ double segment_series(double u, const double (&c)[M])
+{
+    double p = c[M - 1];
+#pragma unroll
+    for (int j = M - 2; j >= 0; --j) p = fma(p, u, c[j]);
+    return p;
+}
+
+__device__ __forceinline__ void plane_setup(PlaneQuad& q, double a, double b, double c, double d, double z2, double w,
+                                            double r0)
+{
+    q.a = a; q.c = c;
+    q.a2 = a * a; q.c2 = c * c;
+    q.G = b - a; q.H = d - c;
+    q.F = q.G * (b + a); q.E = q.H * (d + c);
+    const double D = sqrt64(z2 + (q.a2 + q.c2));
+    q.D2 = D + D;
+    q.pos = D - r0;
+    q.w = w;
+    q.S0 = 0.0;
+    q.S1 = w * q.G * q.H;
+    q.mfirst = (int)floor(q.pos) + 1;
+    q.mlast = (int)ceil(sqrt64(z2 + fma(b, b, d * d)) - r0);
+}
+
+// sqrt(b^2 + n) - b for n >= 0, b >= 0 to full relative precision: n / (b + sqrt(b^2 + n))
+// from the seeds of root and reciprocal (2^-23), then two steps on x^2 + 2 b x = n
+// with the root's seed for the slope
+__device__ __forceinline__ double plane_offset(double n, double b)
+{
+    const double s2 = fmax(fma(b, b, n), Tiny<2>::value);
+    const double y = __builtin_amdgcn_rsq(s2), h = -0.5 * y, b2 = b + b;
+    double x = n * __builtin_amdgcn_rcp(fma(s2, y, b));
+    x = fma(fma(x, x + b2, -n), h, x);
+    return fma(fma(x, x + b2, -n), h, x);
+}
+
+// the area nearer than the outer edge of bin m, mfirst <= m < mlast
+__device__ __forceinline__ double plane_edge(const PlaneQuad& Q, int m, const double* tab)
+{
+    const double t = m - Q.pos, q = t * (t + Q.D2);
+    const double qE = q - Q.E, qF = q - Q.F;
+    const bool onD = qE > 0.0, onC = qF < 0.0;
+    // each end point's offset n / (base + sqrt(base^2 + n)) along the line it is on
+    const double na = onD ? qE : q, nb = onC ? q : qF;
+    const double ba = onD ? Q.a : Q.c, bb = onC ? Q.a : Q.c;
+    const double fa = plane_offset(na, ba), fb = plane_offset(nb, bb);
+    const double pa = onD ? fa : 0.0, va = onD ? Q.H : fa;
+    const double pb = onC ? fb : Q.G, vb = onC ? 0.0 : fb;
+    const double dp = pb - pa, sv = va + vb;
+    const double num = dp + (va - vb), den = fma(2.0, Q.a + Q.c, (pa + pb) + sv);
+    const double x = arc_quotient<2>(num, den), u = x * x;
+    const double K = q + (Q.a2 + Q.c2);
+    double seg;   // K (atan x - x / (1 + x^2))
+    if (__any(!(fabs(x) <= 0.42)))
+        seg = K * (arc_atan<2>(num, den, tab) - x * rcp64_full(1.0 + u));
+    else if (__any(fabs(x) > 0.125))
+        seg = K * (x * u) * segment_series(u, kSegmentHi);
+    else
+        seg = K * (x * u) * segment_series(u, kSegmentLo);
+    return Q.w * fma(pa, Q.H, fma(0.5 * dp, sv, seg));
+}
+
+// ---------------------------------------------------------------------------
+// the walk over a quadrant's bins
+// ---------------------------------------------------------------------------
+
 // hand the bins wlo .. whi of the quadrant to sink(m, area).  Every edge is
 // evaluated on its own, so a walk that the window clips starts there, with the
 // same areas; the first and the last edge of the quadrant lie outside its
 // corners and are set (S0, S1), which also makes every lane's loop one edge shorter
-template <int N, int S, int NW, class Sink>
-__device__ __forceinline__ void arc_sweep(const ArcQuad<N>& q, double r0, int wlo, int whi, const double* tab,
-                                          Sink& sink)
+template <class Quad, class Edge, class Sink>
+__device__ __forceinline__ void sweep_edges(const Quad& q, double r0, int wlo, int whi, Edge edge, Sink& sink)
 {
     const int mb = max(q.mfirst, wlo), me = min(q.mlast, whi);
     if (mb > me) return;
     const bool tail = me == q.mlast;
     const int mend = tail ? me - 1 : me;   // the last edge evaluated
     double s0 = q.S0, r = r0 + mb;
-    if (mb > q.mfirst) s0 = arc_edge<N, S, NW>(q, r - 1.0, tab);
+    if (mb > q.mfirst) s0 = edge(mb - 1, r - 1.0);
     for (int m = mb; m <= mend; ++m, r += 1.0) {
         const auto w = sink.fetch(m);   // what the bin's sum needs from memory, under way while the edge is evaluated
-        const double s1 = arc_edge<N, S, NW>(q, r, tab);
+        const double s1 = edge(m, r);
         sink.add(m, s1 - s0, w);
         s0 = s1;
     }
     if (tail) sink(me, q.S1 - s0);
+}
+
+template <int N, int S, int NW, class Sink>
+__device__ __forceinline__ void arc_sweep(const ArcQuad<N>& q, double r0, int wlo, int whi, const double* tab,
+                                          Sink& sink)
+{
+    sweep_edges(q, r0, wlo, whi, [&](int, double r) { return arc_edge<N, S, NW>(q, r, tab); }, sink);
+}
+
+template <class Sink>
+__device__ __forceinline__ void plane_sweep(const PlaneQuad& q, double r0, int wlo, int whi, const double* tab,
+                                            Sink& sink)
+{
+    sweep_edges(q, r0, wlo, whi, [&](int m, double) { return plane_edge(q, m, tab); }, sink);
 }
 
 // ---------------------------------------------------------------------------

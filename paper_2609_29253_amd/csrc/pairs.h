@@ -108,13 +108,19 @@ struct PlanarPair {
             const double a = i ? U.lo[1] : U.lo[0], b = i ? U.hi[1] : U.hi[0];
             const double c = j ? V.lo[1] : V.lo[0], d = j ? V.hi[1] : V.hi[0];
             const float w = (i ? U.w[1] : U.w[0]) * (j ? V.w[1] : V.w[0]);
-            ArcQuad<0> q;   // the plane's own coordinates, weight 1
-            q.base2 = z2;
-            q.wN = a; q.oN = a * a;
-            q.wF = b; q.oF = b * b;
-            q.P[0] = 0.5 * w; q.Q[0] = w;
-            arc_finish<0, 1>(q, c, d, r0);
-            arc_sweep<0, 1, NW>(q, r0, wlo, whi, tab, sink);
+            if constexpr (NW >= 2) {
+                PlaneQuad q;
+                plane_setup(q, a, b, c, d, z2, w, r0);
+                plane_sweep(q, r0, wlo, whi, tab, sink);
+            } else {
+                ArcQuad<0> q;   // the plane's own coordinates, weight 1
+                q.base2 = z2;
+                q.wN = a; q.oN = a * a;
+                q.wF = b; q.oF = b * b;
+                q.P[0] = 0.5 * w; q.Q[0] = w;
+                arc_finish<0, 1>(q, c, d, r0);
+                arc_sweep<0, 1, NW>(q, r0, wlo, whi, tab, sink);
+            }
         }
     }
 };
