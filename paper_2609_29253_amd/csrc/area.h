@@ -553,21 +553,22 @@ __device__ __forceinline__ double plane_edge(const PlaneQuad& Q, int m, const do
 // ---------------------------------------------------------------------------
 
 // hand the bins wlo .. whi of the quadrant to sink(m, area).  Every edge is
-// evaluated on its own, so a walk that the window clips starts there, with the
-// same areas; the first and the last edge of the quadrant lie outside its
-// corners and are set (S0, S1), which also makes every lane's loop one edge shorter
+// evaluated on its own, from its number, so a walk that the window clips starts
+// there, with the same areas bit for bit; the first and the last edge of the
+// quadrant lie outside its corners and are set (S0, S1), which also makes every
+// lane's loop one edge shorter
 template <class Quad, class Edge, class Sink>
-__device__ __forceinline__ void sweep_edges(const Quad& q, double r0, int wlo, int whi, Edge edge, Sink& sink)
+__device__ __forceinline__ void sweep_edges(const Quad& q, int wlo, int whi, Edge edge, Sink& sink)
 {
     const int mb = max(q.mfirst, wlo), me = min(q.mlast, whi);
     if (mb > me) return;
     const bool tail = me == q.mlast;
     const int mend = tail ? me - 1 : me;   // the last edge evaluated
-    double s0 = q.S0, r = r0 + mb;
-    if (mb > q.mfirst) s0 = edge(mb - 1, r - 1.0);
-    for (int m = mb; m <= mend; ++m, r += 1.0) {
+    double s0 = q.S0;
+    if (mb > q.mfirst) s0 = edge(mb - 1);
+    for (int m = mb; m <= mend; ++m) {
         const auto w = sink.fetch(m);   // what the bin's sum needs from memory, under way while the edge is evaluated
-        const double s1 = edge(m, r);
+        const double s1 = edge(m);
         sink.add(m, s1 - s0, w);
         s0 = s1;
     }
@@ -578,14 +579,13 @@ template <int N, int S, int NW, class Sink>
 __device__ __forceinline__ void arc_sweep(const ArcQuad<N>& q, double r0, int wlo, int whi, const double* tab,
                                           Sink& sink)
 {
-    sweep_edges(q, r0, wlo, whi, [&](int, double r) { return arc_edge<N, S, NW>(q, r, tab); }, sink);
+    sweep_edges(q, wlo, whi, [&](int m) { return arc_edge<N, S, NW>(q, r0 + m, tab); }, sink);
 }
 
 template <class Sink>
-__device__ __forceinline__ void plane_sweep(const PlaneQuad& q, double r0, int wlo, int whi, const double* tab,
-                                            Sink& sink)
+__device__ __forceinline__ void plane_sweep(const PlaneQuad& q, int wlo, int whi, const double* tab, Sink& sink)
 {
-    sweep_edges(q, r0, wlo, whi, [&](int m, double) { return plane_edge(q, m, tab); }, sink);
+    sweep_edges(q, wlo, whi, [&](int m) { return plane_edge(q, m, tab); }, sink);
 }
 
 // ---------------------------------------------------------------------------

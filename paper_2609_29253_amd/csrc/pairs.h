@@ -111,7 +111,7 @@ struct PlanarPair {
             if constexpr (NW >= 2) {
                 PlaneQuad q;
                 plane_setup(q, a, b, c, d, z2, w, r0);
-                plane_sweep(q, r0, wlo, whi, tab, sink);
+                plane_sweep(q, wlo, whi, tab, sink);
             } else {
                 ArcQuad<0> q;   // the plane's own coordinates, weight 1
                 q.base2 = z2;
