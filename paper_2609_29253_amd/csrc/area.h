@@ -183,30 +183,36 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 
 // h's factor (1 - x)^(-1/2) = (1 - xc)^(-1/2) (1 - tau)^(-1/2), tau = (x - xc) /
 // (1 - xc): interpolants of degree n at Chebyshev nodes on |tau| <= eta, by level.
-// Relative error with FP32 input and output 1.6e-9, 1.9e-9 and 7.5e-10: their signals
-// round at 6e-8, and these errors pass to them undivided (each bin's area changes
-// by that share); with FP64 6.2e-14, 1.0e-13 and 3.3e-13.  kappa bounds vmax^2 / (mu
-// (1 - xc)), whose n-th power multiplies the roundings of the J_j.
+// Relative error with FP32 input and output 2.2e-11, 2.3e-11 and 5.7e-11, three orders
+// below the output's rounding and no more than Carlson's integral leaves there (worst
+// bin of a pair over its largest, median / 95 % / worst, Carlson and this: elements
+// of a scan at U = 1 1.7e-11 / 2.4e-10 / 2.3e-9 and 2.0e-11 / 7e-11 / 1.1e-10, at U = 11 2.1e-10 /
+// 1.9e-9 / 2e-8 and 3.3e-11 / 5e-10 / 1e-9, of an arc 5e-8 / 1.4e-7 / 1.7e-7 and 1.2e-11 /
+// 1.7e-11 / 2e-11); with FP64 6.2e-14, 1.0e-13 and 3.3e-13.  Degrees 4, 5, 7 (1.6e-9 at
+// U = 1, whatever the element) take 62.1 and 64.6 ms on 128^3 x 256 cylinders where
+// these take 66.1 and 69.0, 67.6 on the scan of 200^3 x 64 where these take 72.8.  kappa
+// bounds vmax^2 / (mu (1 - xc)), whose n-th power multiplies the roundings of the J_j.
 template <int NW, int LEVEL> struct Weight;
 template <> struct Weight<1, 0> {
-    static constexpr int n = 4;
-    static constexpr double eta = 0.04, kappa = 3.2;
+    static constexpr int n = 5;
+    static constexpr double eta = 0.038, kappa = 2.6;
     static constexpr double c[n + 1] = {
-        1.0, 0.4999998027893683, 0.3749998192165893, 0.31299285870394444, 0.2738893011398508};
+        1.0000000000212659, 0.5000000000197475, 0.3749997349316204, 0.31249975385743234, 0.27392681105161915,
+        0.24654812125416245};
 };
 template <> struct Weight<1, 1> {
-    static constexpr int n = 5;
-    static constexpr double eta = 0.08, kappa = 2.6;
+    static constexpr int n = 7;
+    static constexpr double eta = 0.104, kappa = 2.0;
     static constexpr double c[n + 1] = {
-        1.0000000018635444, 0.5000000017306818, 0.3749947604041674, 0.31249513399010315, 0.2756167786712076,
-        0.24811758344361434};
+        0.9999999999785899, 0.4999999999797752, 0.37500006332410346, 0.3125000598183644, 0.27340827460690964,
+        0.24606614306016883, 0.22989139768446637, 0.2135395082670361};
 };
 template <> struct Weight<1, 2> {
-    static constexpr int n = 7;
-    static constexpr double eta = 0.16, kappa = 2.0;
+    static constexpr int n = 8;
+    static constexpr double eta = 0.16, kappa = 1.8;
     static constexpr double c[n + 1] = {
-        0.9999999993097828, 0.49999999934780515, 0.375000862151671, 0.31250081465170293, 0.27326976417167687,
-        0.24593526203177093, 0.23596719691165274, 0.21928054205212558};
+        1.0, 0.49999999704787307, 0.3749999971941834, 0.3125015348867947, 0.27343895879424956,
+        0.2458789227748675, 0.2253817687557605, 0.22053917177169305, 0.20689706937941357};
 };
 template <> struct Weight<2, 0> {
     static constexpr int n = 7;
