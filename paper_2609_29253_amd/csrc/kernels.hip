@@ -375,6 +375,7 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
             if (nz) pair_range<SHAPE>(T, x, P.r0, lo, hi);   // lanes whose volumes are all zero add nothing
             wave_window(P, lo, hi, wlo, whi);
             pair.setup(T, x, P.r0);
+            pair.agree(valid);
         }
         for (int plo = wlo; plo <= whi; plo += HW) {
             const int phi = min(whi, plo + HW - 1);
@@ -523,6 +524,7 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
                 double x[3];
                 frame_coords(T, Bk.ix, Bk.iy, Bk.iz, x);
                 pair.setup(T, x, P.r0);
+                pair.agree(Bk.valid);
             }
             if (nz) {
                 Scatter<NB> sink;
@@ -533,8 +535,7 @@ __global__ __launch_bounds__(kThreads, (closed_waves<SHAPE, AT, NB>())) void k_f
                 for (int v = 0; v < NB; ++v) sink.p0[v] = p0[v];
                 // every edge is evaluated on its own (those outside a quadrant
                 // are set, as in the cube forward), so a tile's areas are the
-                // cube forward's; a cylinder wave's choice between the degrees
-                // of the weight differs by the polynomials' error only
+                // cube forward's (see ArcCylinderPair::agree)
                 pair.sweep(tlo, thi, sink, P.r0);
             }
         }
@@ -622,6 +623,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
             if (valid) pair_range<SHAPE>(T, x, P.r0, lo, hi);
             wave_window(P, lo, hi, wlo, whi);
             pair.setup(T, x, P.r0);
+            pair.agree(valid);
         }
         for (int plo = wlo; plo <= whi; plo += HB) {
             const int phi = min(whi, plo + HB - 1);
@@ -930,6 +932,7 @@ __global__ __launch_bounds__(kThreads) void k_count(KParams P, int quad, unsigne
             typename PairOf<SHAPE, double, kIlExact>::type pair;
             pair.bind(box, nullptr, tab, P.tr + P.kperm[kk], Bk.ix, Bk.iy, Bk.iz);
             pair.setup(T, x, P.r0);
+            pair.agree(true);
             pair.sweep(lo, hi, sink, P.r0);
             evals += sink.n;
             pairs += 1;

@@ -86,6 +86,7 @@ struct PlanarPair {
         fold_line(-L2 - x[1], L2 - x[1], V);
         z2 = x[2] * x[2];
     }
+    __device__ __forceinline__ void agree(bool) {}
     // bins wlo .. whi of each quadrant reach the sink; each edge is evaluated
     // on its own, so the walk starts at max(mfirst, wlo)
     template <class Sink>
@@ -238,6 +239,7 @@ struct CylinderPair {
         c = box[(4 + 2 * j) * STRIDE]; d = box[(5 + 2 * j) * STRIDE];
         w = (double)((1 + ((wbits >> i) & 1)) * (1 + ((wbits >> (2 + j)) & 1)));
     }
+    __device__ __forceinline__ void agree(bool) {}
     // bins wlo .. whi of each quadrant reach the sink; each edge is evaluated
     // on its own, so the walk starts at max(mfirst, wlo)
     template <class Sink>
@@ -320,6 +322,7 @@ struct ArcCylinderPair {
     int bits;                // bit 0 / 1: U / V interval 0 has weight 2; bit 2 / 3: U interval 0 ends at
                              // u = 0 / pi; bits 4 / 5: the weight's level is at least 1 / 2; bits 6-8:
                              // level 0 / 1 / 2 does not serve, all of them for Carlson's path
+    int level;               // the pair's own, the wave's after agree()
     const TrDev* tr;         // the pair, for Carlson's path
     int ix, iy, iz;
     __device__ __forceinline__ void bind(double* table, const double2*, const double* t, const TrDev* T, int x, int y,
@@ -357,10 +360,12 @@ struct ArcCylinderPair {
         const double vmax = V.n == 2 ? V.hi[1] : V.hi[0];
         bits = (in0 || inpi ? 1 : 0) | (V.n == 2 ? 2 : 0) | (in0 ? 4 : 0) | (inpi ? 8 : 0);
         const ArcFit fit = arc_fit<NW>(R, rho, c0, c1, cm, cp, uok[0], uok[1], vmax, inpi);
+        level = 0;
         if (!fit.fits()) {
             bits |= 7 << 6;
             return;
         }
+        level = fit.least;
         // the non-empty quadrants in decreasing order of their number of bins
         // (nearest to farthest corner, estimated in FP32): the wave steps
         // through every lane's t-th quadrant together, so the lanes' longest
@@ -394,6 +399,17 @@ struct ArcCylinderPair {
         box[0 * STRIDE] = cm; box[1 * STRIDE] = fabs(sm);
         box[2 * STRIDE] = cp; box[3 * STRIDE] = fabs(sp);
         box[4 * STRIDE] = V.lo[0]; box[5 * STRIDE] = V.hi[0]; box[6 * STRIDE] = V.hi[1];
+    }
+    // One level of the weight for the wave's lanes, which are neighbouring voxels; a lane
+    // it does not serve takes Carlson's path.  All the cube's voxels take part, whether
+    // or not they have a coefficient, so the forward of any volume, alone or beside
+    // others, by cubes or by time tiles, and the adjoint use the same areas (to the
+    // rounding of the arc's angle, whose series the active lanes choose: 2e-15 of a
+    // signal).  The sparse forward's waves are of listed voxels: its areas differ by
+    // the weight's error.
+    __device__ __forceinline__ void agree(bool valid)
+    {
+        level = __any(valid && (bits & 32)) ? 2 : __any(valid && (bits & 16)) ? 1 : 0;
     }
     // p(om) = scale (1 - x)^(-1/2): Weight's polynomial in tau = al om + be, expanded
     template <class Wt>
@@ -466,11 +482,9 @@ struct ArcCylinderPair {
     template <class Sink>
     __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
     {
-        // one level for the wave's lanes, which are neighbouring voxels; a lane it
-        // does not serve takes Carlson's path
-        if (__any(bits & 32))
+        if (level == 2)
             arcs_or_carlson<2>(wlo, whi, sink, r0);
-        else if (__any(bits & 16))
+        else if (level == 1)
             arcs_or_carlson<1>(wlo, whi, sink, r0);
         else
             arcs_or_carlson<0>(wlo, whi, sink, r0);
