@@ -23,6 +23,7 @@
 #include "kernels.h"
 #include "pairs.h"
 #include "patop.h"
+#include "plan.h"
 
 using namespace patop;
 using patop::geom::bounding_sphere;
@@ -403,15 +404,10 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     const int ncubes = (int)(((grid->n[0] + 3) / 4) * ((grid->n[1] + 3) / 4) * ((grid->n[2] + 3) / 4));
     // Work-groups of a brick's size that a launch is split into at least, by chunks
     // of transducers.  The forward adds into f with atomics whatever its chunks, and
-    // eight times as many as the adjoint's shorten its last round (128^3 x 256 cylinders
+    // eight times as many as the adjoint's (adjoint_chunk) shorten its last round (128^3 x 256 cylinders
     // 62.4 ms with four times, 61.2 with eight, 61.0 with sixteen; quadrature on 64^3 x 64
-    // 2.83 ms with one, 2.56 with four or eight, on 128^3 x 64 24.9, 24.3 and 24.0).  The
-    // adjoint's sum over a voxel's transducers has one order where at most two terms
-    // are added to the zero that it starts from: two chunks where one work-group
-    // could see every transducer but the waves are few (128^3 x 256 cylinders 67.3 ->
-    // 64.4 ms, 8 x 128^3 x 256 rectangles 14.7 -> 14.0, quadrature on 128^3 x 64 15.2 ->
-    // 14.7: half the last round); not with both shapes, whose sums would have four.
-    const int target_wg = 4096, target_fwd = 32768;
+    // 2.83 ms with one, 2.56 with four or eight, on 128^3 x 64 24.9, 24.3 and 24.0).
+    const int target_fwd = 32768;
 
     // ---- device allocations
     const size_t rs = p.precision == PAT_FP64 ? sizeof(double) : sizeof(float);
@@ -507,14 +503,10 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.shape = s;
         Gp.kperm = c->d_kperm + off;
         Gp.nk = nk;
-        auto chunk = [&](int target) {
-            const int nchunks = std::max(1, std::min(nk, (target + nbricks - 1) / nbricks));
-            return (nk + nchunks - 1) / nchunks;
-        };
-        Gp.kchunk_fwd = chunk(target_fwd);
-        Gp.kchunk_adj = chunk(target_wg);
-        if (nbricks < 16384 && (nplan == 0 || ncyl == 0))
-            Gp.kchunk_adj = std::min(Gp.kchunk_adj, (nk + 1) / 2);
+        const int nchunks = std::max(1, std::min(nk, (target_fwd + nbricks - 1) / nbricks));
+        Gp.kchunk_fwd = (nk + nchunks - 1) / nchunks;
+        Gp.kchunk_adj = adjoint_chunk(nk, nbricks, nplan == 0 || ncyl == 0, mean_shells(T.data(), perm.data() + off, nk, B),
+                                      p.max_batch);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
                      arc_share(T.data(), perm.data() + off, nk, *grid) <
                          ((int64_t)ncubes * nk < 24576 ? 1.0 : 0.2);

@@ -1,0 +1,64 @@
+// Rules of the launch plan that follow from the geometry alone, on the host.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+
+#include "patop_internal.h"
+
+namespace patop {
+
+// Up to kSampled transducers of n, spread over them, stand for all (an array's
+// elements are alike, its set-up should not grow by their number)
+constexpr int kSampled = 32;
+inline int sample_count(int n) { return std::min(n, kSampled); }
+inline int sample_index(int i, int n) { return n <= kSampled ? i : (int)((int64_t)i * (n - 1) / (kSampled - 1)); }
+
+// coordinate of the q-th of four sampled voxels along an axis of n
+inline double sample_voxel(int64_t n, int q) { return (double)(n - 1) * (q + 0.5) / 4.0; }
+
+// Work of a voxel-transducer pair, on average over 4 x 4 x 4 voxels of the grid and
+// sampled transducers: shells of the distance window that are kept (P.r0, P.Jlo,
+// P.Jhi), or the quadrature's points where any shell is.
+inline double mean_shells(const TrDev* T, const int32_t* perm, int n, const KParams& P)
+{
+    double sum = 0.0;
+    const int count = sample_count(n);
+    for (int i = 0; i < count; ++i) {
+        const TrDev& t = T[perm[sample_index(i, n)]];
+        for (int v = 0; v < 64; ++v) {
+            double d2 = 0.0;
+            for (int a = 0; a < 3; ++a) {
+                const double d = P.origin[a] + P.w * sample_voxel(P.n[a], (v >> (2 * a)) & 3) - t.cen[a];
+                d2 += d * d;
+            }
+            const double d = std::sqrt(d2) - P.r0;
+            const double lo = std::max(std::floor(d - t.rad), (double)P.Jlo), hi = std::min(std::ceil(d + t.rad), (double)P.Jhi);
+            if (lo <= hi) sum += P.qn1 > 0 ? (double)P.qn1 * P.qn2 : hi - lo + 1.0;
+        }
+    }
+    return sum / (64.0 * count);
+}
+
+// Transducers per work-group of the adjoint: as many work-groups as 4096 of a brick's
+// size, and two chunks where one work-group could see every transducer but the waves
+// are few and the work is enough.  A voxel's sum has one order where at most two
+// terms are added to the zero that it starts from, hence two, and only for an
+// array of one shape (two shapes would make four).  Two chunks halve the last
+// round (128^3 x 256 cylinders 67.5 -> 64.6 ms, quadrature 61.8 -> 59.5, 256 rectangles
+// 10.6 -> 10.3) at the cost of sums cleared, added and cast in memory, about 18 ps per voxel
+// and volume, against some 15 ps of the last round saved per thousand shells and
+// voxel: 128^3 rectangles, one volume, 8 (W = 380 shells) 0.347 -> 0.350 ms, 16 0.677 ->
+// 0.669; eight volumes, 8 0.47 -> 0.54, 32 (W = 1540) 1.83 -> 1.82; 32 with 128 samples kept
+// 0.21 -> 0.42; cylinders, one volume, 3 (W = 670) 0.81 -> 0.80, eight, 4 1.29 -> 1.34, 8 (W = 1800)
+// 2.60 -> 2.58.  So from W = 512 (volumes + 1) on.
+inline int adjoint_chunk(int nk, int64_t nbricks, bool one_shape, double shells, int volumes)
+{
+    const int64_t target = 4096;
+    const int64_t nchunks = std::max<int64_t>(1, std::min<int64_t>(nk, (target + nbricks - 1) / nbricks));
+    const int chunk = (int)((nk + nchunks - 1) / nchunks);
+    if (one_shape && nbricks < 4 * target && nk * shells >= 512.0 * (volumes + 1)) return std::min(chunk, (nk + 1) / 2);
+    return chunk;
+}
+
+}  // namespace patop

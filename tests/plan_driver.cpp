@@ -1,0 +1,42 @@
+// The launch plan's rules on the host, for their CPU tests.
+#include <hip/hip_runtime.h>
+
+#include <vector>
+
+#include "plan.h"
+
+using namespace patop;
+
+static std::vector<TrDev> table(const double* sphere, int nk, std::vector<int32_t>& perm)
+{
+    std::vector<TrDev> T(nk);
+    for (int k = 0; k < nk; ++k) {
+        std::memset(&T[k], 0, sizeof(TrDev));
+        for (int a = 0; a < 3; ++a) T[k].cen[a] = sphere[4 * k + a];
+        T[k].rad = sphere[4 * k + 3];
+        perm.push_back(k);
+    }
+    return T;
+}
+
+// bounding spheres of nk transducers (in shells), a cube of n^3 voxels around 0
+extern "C" int adjoint_chunk_of(const double* sphere, int nk, int n, double w, double r0, int jlo, int jhi, int points,
+                                int one_shape, int volumes)
+{
+    std::vector<int32_t> perm;
+    const auto T = table(sphere, nk, perm);
+    KParams P;
+    std::memset(&P, 0, sizeof P);
+    for (int a = 0; a < 3; ++a) {
+        P.n[a] = n;
+        P.origin[a] = -0.5 * (n - 1) * w;
+    }
+    P.w = w;
+    P.r0 = r0;
+    P.Jlo = jlo;
+    P.Jhi = jhi;
+    P.qn1 = points;
+    P.qn2 = points;
+    const int64_t nbricks = (int64_t)((n + 7) / 8) * ((n + 7) / 8) * ((n + 3) / 4);
+    return adjoint_chunk(nk, nbricks, one_shape, mean_shells(T.data(), perm.data(), nk, P), volumes);
+}

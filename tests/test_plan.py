@@ -1,0 +1,49 @@
+"""The launch plan's rules on the CPU (plan.h compiled for the host)."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import pat_inputs as P
+from conftest import ROOT
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+pd = ctypes.POINTER(ctypes.c_double)
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-w", "-shared", "-fPIC", "-I", os.path.join(ROOT, "tests", "hip_shim"),
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2609_29253_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "plan_driver.cpp"), "-o", so], check=True)
+    return ctypes.CDLL(so)
+
+
+def chunk(plan, K, volumes=1, n=128, rad=23.6, kept=2000, points=0, one_shape=True):
+    """The adjoint's chunk: elements of radius `rad` shells on a sphere of 40 mm at 50 MHz."""
+    s = np.concatenate([P.fibonacci_points(K, 40e-3) / 30e-6, np.full((K, 1), rad)], 1)
+    s = np.ascontiguousarray(s)
+    fn = plan.adjoint_chunk_of
+    fn.argtypes = [pd, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_double] + [ctypes.c_int] * 5
+    return fn(s.ctypes.data_as(pd), K, n, 0.1e-3 / 30e-6, 800.0, -40, kept, points, int(one_shape), volumes)
+
+
+def test_adjoint_stays_whole_where_its_work_is_small(plan):
+    """Two chunks cost the clearing, the adding and the cast of FP64 sums: 1.2 to 7 times
+    the whole adjoint's time with few transducers, many volumes or a short window."""
+    for K, volumes in ((1, 1), (2, 1), (8, 1), (2, 8), (8, 8), (32, 8)):
+        assert chunk(plan, K, volumes) == K
+    assert chunk(plan, 32, 1, kept=0) == 32 and chunk(plan, 32, 8, kept=100) == 32     # few samples kept
+    assert chunk(plan, 2, 8, rad=112.0) == 2 and chunk(plan, 4, 8, points=16) == 4
+    assert chunk(plan, 256, 8, n=256) == 256 and chunk(plan, 24, 1, one_shape=False) == 24
+
+
+def test_adjoint_splits_where_it_pays(plan):
+    for K, volumes, kw in ((256, 1, {}), (256, 8, {}), (33, 1, {}), (8, 1, dict(rad=112.0)), (64, 8, dict(rad=112.0)),
+                           (8, 1, dict(points=16))):
+        assert chunk(plan, K, volumes, **kw) == (K + 1) // 2, (K, volumes, kw)
+    assert chunk(plan, 64, 1, n=32) == 2       # below 4096 bricks by their number, as many chunks as fill the device
