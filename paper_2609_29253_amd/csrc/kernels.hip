@@ -35,6 +35,7 @@
 #include "area.h"
 #include "kernels.h"
 #include "pairs.h"
+#include "plan.h"
 
 namespace patop {
 
@@ -1381,7 +1382,7 @@ hipError_t adjoint_t(const LaunchPlan& L, const Real* sig, Real* coef, int B, hi
     Real* W = (Real*)L.W;
     const bool direct = L.ngroups == 1 && L.groups[0].kchunk_adj >= L.groups[0].nk;
     const int64_t nz = (int64_t)B * L.base.N;
-    dim3 g1((unsigned)((L.base.Mcount + 255) / 256), L.base.K, B);
+    const dim3 g1((unsigned)adjw_blocks(L.base.Mcount, (int64_t)L.base.K * B, direct ? 0 : nz), L.base.K, B);
     k_adjw<Real><<<g1, 256, 0, s>>>(sig, L.scale, L.G, L.jlo, L.jcnt, L.U, L.L, L.base.K, L.base.Mlo, L.base.Mcount,
                                     W, L.z64, direct ? 0 : nz);
     if ((e = hipGetLastError()) != hipSuccess) return e;

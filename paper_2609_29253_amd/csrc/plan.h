@@ -61,4 +61,14 @@ inline int adjoint_chunk(int nk, int64_t nbricks, bool one_shape, double shells,
     return chunk;
 }
 
+// Work-groups of 256 per transducer and volume of the launch that forms W and clears the
+// adjoint's sums: what W's bins need, or, where the bins are few and the sums many (a
+// short window over a large grid: 2 transducers x 256^3 voxels x 64 samples, 1.59 ms where a
+// launch of its own to clear them took 0.56), what fills the device: 4096 in all.
+inline int64_t adjw_blocks(int64_t bins, int64_t rows, int64_t sums)
+{
+    const int64_t fill = std::min<int64_t>(4096, (sums + 255) / 256);
+    return std::max((bins + 255) / 256, (fill + rows - 1) / rows);
+}
+
 }  // namespace patop

@@ -40,3 +40,5 @@ extern "C" int adjoint_chunk_of(const double* sphere, int nk, int n, double w, d
     const int64_t nbricks = (int64_t)((n + 7) / 8) * ((n + 7) / 8) * ((n + 3) / 4);
     return adjoint_chunk(nk, nbricks, one_shape, mean_shells(T.data(), perm.data(), nk, P), volumes);
 }
+
+extern "C" long adjw_blocks_of(long bins, long rows, long sums) { return adjw_blocks(bins, rows, sums); }

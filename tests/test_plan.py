@@ -47,3 +47,18 @@ def test_adjoint_splits_where_it_pays(plan):
                            (8, 1, dict(points=16))):
         assert chunk(plan, K, volumes, **kw) == (K + 1) // 2, (K, volumes, kw)
     assert chunk(plan, 64, 1, n=32) == 2       # below 4096 bricks by their number, as many chunks as fill the device
+
+
+def test_clearing_launch_fills_the_device(plan):
+    """Bins few and sums many: as many work-groups as a fill takes (4096, or one per 256 sums);
+    never fewer than the bins need, and no more where there is nothing to clear."""
+    fn = plan.adjw_blocks_of
+    fn.argtypes, fn.restype = [ctypes.c_long] * 3, ctypes.c_long
+    for bins in (1, 190, 256, 257, 2200, 30000):
+        for rows in (1, 2, 3, 64, 2048):
+            need = -(-bins // 256)
+            assert fn(bins, rows, 0) == need
+            for sums in (1, 1000, 8 * 128 ** 3, 256 ** 3):
+                got, fill = fn(bins, rows, sums), min(4096, -(-sums // 256))
+                assert got >= need and got * rows >= fill
+                assert got == need or (got - 1) * rows < fill
