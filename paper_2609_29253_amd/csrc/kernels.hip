@@ -375,6 +375,7 @@ __device__ __forceinline__ void fwd_wave_voxels(const KParams& P, int ix, int iy
             int lo = 0x7fffffff, hi = -0x7fffffff - 1;
             if (nz) pair_range<SHAPE>(T, x, P.r0, lo, hi);   // lanes whose volumes are all zero add nothing
             wave_window(P, lo, hi, wlo, whi);
+            if (wlo > whi) continue;   // no shell kept: a cylinder's set-up costs more than all else here
             pair.setup(T, x, P.r0);
             pair.agree(valid);
         }
@@ -623,6 +624,7 @@ __global__ __launch_bounds__(kWave, (closed_waves<SHAPE, AT, NB>())) void k_adj_
             int lo = 0x7fffffff, hi = -0x7fffffff - 1;
             if (valid) pair_range<SHAPE>(T, x, P.r0, lo, hi);
             wave_window(P, lo, hi, wlo, whi);
+            if (wlo > whi) continue;   // no shell kept: a cylinder's set-up costs more than all else here
             pair.setup(T, x, P.r0);
             pair.agree(valid);
         }
