@@ -21,7 +21,6 @@
 
 #include "geometry.h"
 #include "kernels.h"
-#include "pairs.h"
 #include "patop.h"
 #include "plan.h"
 
@@ -155,40 +154,6 @@ void free_dev(pat_ctx* c)
     }
     c->ready = false;
     c->ws_bytes = 0;
-}
-
-// The share of the cylinders' pairs that the weighted areas serve with FP64 input
-// and output (arc_fit), on 4 x 4 x 4 voxels spread over the grid.  Below 0.2
-// the kernels that evaluate every pair by Carlson's integral are faster, since
-// waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
-// the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
-// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).  A launch of
-// few waves lasts as long as its slowest ones, which hold both kinds, so below 24576
-// every sampled pair has to be served (elements of a scan, A / A^T, Carlson against
-// mixed: 22 x 14 x 22 x 26, 3744 waves, 46 / 46 against 67 / 67 us; 28^3 x 64, 21952
-// waves, 195 / 215 against 210 / 243 us; 32^3 x 64, 32768 waves, 339 / 354 against
-// 324 / 337 us; 80^3 x 64 6.9 / 7.5 against 4.7 / 5.1 ms).
-double arc_share(const TrDev* T, const int32_t* perm, int n, const pat_grid& grid)
-{
-    int64_t fit = 0;
-    for (int i = 0; i < n; ++i) {
-        const TrDev& t = T[perm[i]];
-        for (int v = 0; v < 64; ++v) {
-            double x[3];
-            for (int a = 0; a < 3; ++a) {
-                x[a] = t.base[a];
-                for (int q = 0; q < 3; ++q) x[a] += t.g[a][q] * (double)(grid.n[q] - 1) * (((v >> (2 * q)) & 3) + 0.5) / 4.0;
-            }
-            const double rho = std::hypot(x[0], x[1]), ct = rho > 0.0 ? x[0] / rho : 1.0, st = rho > 0.0 ? std::fabs(x[1]) / rho : 0.0;
-            const double cm = ct * t.cth + st * t.sth, sm = st * t.cth - ct * t.sth;
-            const double cp = ct * t.cth - st * t.sth, sp = st * t.cth + ct * t.sth;
-            const bool in0 = sm < 0.0, inpi = !in0 && sp < 0.0;
-            fit += arc_fit<2>(t.p[0], rho, in0 ? 1.0 : inpi ? cp : cm, in0 ? cm : inpi ? -1.0 : cp, cm, cp, true, in0 || inpi,
-                              std::fabs(x[2]) + t.p[2], inpi)
-                       .fits();
-        }
-    }
-    return (double)fit / (64.0 * n);
 }
 
 struct DevGuard {
@@ -508,7 +473,7 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.kchunk_adj = adjoint_chunk(nk, nbricks, nplan == 0 || ncyl == 0, mean_shells(T.data(), perm.data() + off, nk, B),
                                       p.max_batch);
         Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
-                     arc_share(T.data(), perm.data() + off, nk, *grid) <
+                     arc_share<2>(T.data(), perm.data() + off, nk, B) <
                          ((int64_t)ncubes * nk < 24576 ? 1.0 : 0.2);
         off += nk;
     }

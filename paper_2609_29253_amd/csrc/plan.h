@@ -4,12 +4,13 @@
 #include <algorithm>
 #include <cmath>
 
-#include "patop_internal.h"
+#include "pairs.h"
 
 namespace patop {
 
-// Up to kSampled transducers of n, spread over them, stand for all (an array's
-// elements are alike, its set-up should not grow by their number)
+// Up to kSampled transducers of n, spread over them, stand for all: an array's
+// elements are alike, and its set-up should not grow by a rule's cost (arc_share over all
+// of 512 cylinders took 0.63 ms of 1.43, of 16384 20 of 43)
 constexpr int kSampled = 32;
 inline int sample_count(int n) { return std::min(n, kSampled); }
 inline int sample_index(int i, int n) { return n <= kSampled ? i : (int)((int64_t)i * (n - 1) / (kSampled - 1)); }
@@ -38,6 +39,42 @@ inline double mean_shells(const TrDev* T, const int32_t* perm, int n, const KPar
         }
     }
     return sum / (64.0 * count);
+}
+
+// The share of the cylinders' pairs that the weighted areas serve (arc_fit), on the
+// same voxels and transducers.  With FP64 input and output, below 0.2
+// the kernels that evaluate every pair by Carlson's integral are faster, since
+// waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
+// the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
+// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).  A launch of
+// few waves lasts as long as its slowest ones, which hold both kinds, so below 24576
+// every sampled pair has to be served (elements of a scan, A / A^T, Carlson against
+// mixed: 22 x 14 x 22 x 26, 3744 waves, 46 / 46 against 67 / 67 us; 28^3 x 64, 21952
+// waves, 195 / 215 against 210 / 243 us; 32^3 x 64, 32768 waves, 339 / 354 against
+// 324 / 337 us; 80^3 x 64 6.9 / 7.5 against 4.7 / 5.1 ms).
+template <int NW>
+inline double arc_share(const TrDev* T, const int32_t* perm, int n, const KParams& P)
+{
+    int64_t fit = 0;
+    const int count = sample_count(n);
+    for (int i = 0; i < count; ++i) {
+        const TrDev& t = T[perm[sample_index(i, n)]];
+        for (int v = 0; v < 64; ++v) {
+            double x[3];
+            for (int a = 0; a < 3; ++a) {
+                x[a] = t.base[a];
+                for (int q = 0; q < 3; ++q) x[a] += t.g[a][q] * sample_voxel(P.n[q], (v >> (2 * q)) & 3);
+            }
+            const double rho = std::hypot(x[0], x[1]), ct = rho > 0.0 ? x[0] / rho : 1.0, st = rho > 0.0 ? std::fabs(x[1]) / rho : 0.0;
+            const double cm = ct * t.cth + st * t.sth, sm = st * t.cth - ct * t.sth;
+            const double cp = ct * t.cth - st * t.sth, sp = st * t.cth + ct * t.sth;
+            const bool in0 = sm < 0.0, inpi = !in0 && sp < 0.0;
+            fit += arc_fit<NW>(t.p[0], rho, in0 ? 1.0 : inpi ? cp : cm, in0 ? cm : inpi ? -1.0 : cp, cm, cp, true, in0 || inpi,
+                               std::fabs(x[2]) + t.p[2], inpi)
+                       .fits();
+        }
+    }
+    return (double)fit / (64.0 * count);
 }
 
 // Transducers per work-group of the adjoint: as many work-groups as 4096 of a brick's

@@ -3,7 +3,10 @@
 
 #include <vector>
 
+// area.h writes two FMAs as instructions; here they are what they say
+#define asm(...) r = fma(a, b, c)
 #include "plan.h"
+#undef asm
 
 using namespace patop;
 
@@ -42,3 +45,26 @@ extern "C" int adjoint_chunk_of(const double* sphere, int nk, int n, double w, d
 }
 
 extern "C" long adjw_blocks_of(long bins, long rows, long sums) { return adjw_blocks(bins, rows, sums); }
+
+// cylinders (radius, theta_max, half length, frame coordinates of voxel 0), a cube of n^3
+// voxels `w` apart along the frame's axes
+extern "C" double arc_share_of(const double* cyl, int nk, int n, double w, int fp64)
+{
+    std::vector<TrDev> T(nk);
+    std::vector<int32_t> perm;
+    for (int k = 0; k < nk; ++k) {
+        std::memset(&T[k], 0, sizeof(TrDev));
+        for (int a = 0; a < 3; ++a) {
+            T[k].p[a] = cyl[6 * k + a];
+            T[k].base[a] = cyl[6 * k + 3 + a];
+            T[k].g[a][a] = w;
+        }
+        T[k].cth = std::cos(T[k].p[1]);
+        T[k].sth = std::sin(T[k].p[1]);
+        perm.push_back(k);
+    }
+    KParams P;
+    std::memset(&P, 0, sizeof P);
+    for (int a = 0; a < 3; ++a) P.n[a] = n;
+    return arc_share<2>(T.data(), perm.data(), nk, P);
+}
