@@ -472,9 +472,12 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
         Gp.kchunk_fwd = (nk + nchunks - 1) / nchunks;
         Gp.kchunk_adj = adjoint_chunk(nk, nbricks, nplan == 0 || ncyl == 0, mean_shells(T.data(), perm.data() + off, nk, B),
                                       p.max_batch);
-        Gp.carlson = s == 1 && p.precision == PAT_FP64 && p.area_mode == PAT_AREA_CLOSED &&
-                     arc_share<2>(T.data(), perm.data() + off, nk, B) <
-                         ((int64_t)ncubes * nk < 24576 ? 1.0 : 0.2);
+        if (s == 1 && p.area_mode == PAT_AREA_CLOSED) {
+            const bool fp64 = p.precision == PAT_FP64;
+            const int32_t* own = perm.data() + off;
+            Gp.carlson = carlson_only(fp64 ? arc_share<2>(T.data(), own, nk, B) : arc_share<1>(T.data(), own, nk, B),
+                                      (int64_t)ncubes * nk, fp64);
+        }
         off += nk;
     }
     Lp.nbricks = nbricks;

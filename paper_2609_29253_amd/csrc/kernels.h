@@ -14,7 +14,7 @@ struct ShapeGroup {
     int kchunk_fwd, kchunk_adj;
     const int32_t* items;   // (transducer, time tile) forward: items kk ntiles + t, largest estimated cost
     int nitems;             // first (nk ntiles of them); null when that forward is off
-    bool carlson;           // FP64 cylinders, exact I_l: the group's pairs by Carlson's integral alone
+    bool carlson;           // cylinders, exact I_l: the group's pairs by Carlson's integral alone
 };
 
 struct LaunchPlan {

@@ -1234,8 +1234,7 @@ hipError_t fwd_tile_cyl(int mode, bool carlson, int nb, const KParams& P, const 
         return fwd_tile_nb<1, double, Real, kIlTrapezoid>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
     if (mode == 3)
         return fwd_tile_nb<1, double, Real, kIlTable>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
-    if constexpr (sizeof(Real) == 8)
-        if (carlson) return fwd_tile_nb<1, double, Real, kIlCarlson>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
+    if (carlson) return fwd_tile_nb<1, double, Real, kIlCarlson>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
     return fwd_tile_nb<1, double, Real, kIlExact>(nb, P, items, nitems, tile, ntiles, nbricks, coef, f, s);
 }
 
@@ -1245,8 +1244,7 @@ hipError_t fwd_sparse_cyl(int mode, bool carlson, int nb, dim3 grid, const KPara
 {
     if (mode == 2) return fwd_sparse_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, coef, f, s);
     if (mode == 3) return fwd_sparse_nb<1, double, Real, kIlTable>(nb, grid, P, coef, f, s);
-    if constexpr (sizeof(Real) == 8)
-        if (carlson) return fwd_sparse_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
+    if (carlson) return fwd_sparse_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
     return fwd_sparse_nb<1, double, Real, kIlExact>(nb, grid, P, coef, f, s);
 }
 
@@ -1256,8 +1254,7 @@ hipError_t fwd_wave_cyl(int mode, bool carlson, int nb, dim3 grid, const KParams
 {
     if (mode == 2) return fwd_wave_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, coef, f, s);
     if (mode == 3) return fwd_wave_nb<1, double, Real, kIlTable>(nb, grid, P, coef, f, s);
-    if constexpr (sizeof(Real) == 8)
-        if (carlson) return fwd_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
+    if (carlson) return fwd_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, coef, f, s);
     return fwd_wave_nb<1, double, Real, kIlExact>(nb, grid, P, coef, f, s);
 }
 
@@ -1267,8 +1264,7 @@ hipError_t adj_wave_cyl(int mode, bool carlson, int nb, dim3 grid, const KParams
 {
     if (mode == 2) return adj_wave_nb<1, double, Real, kIlTrapezoid>(nb, grid, P, W, out, z64, direct, s);
     if (mode == 3) return adj_wave_nb<1, double, Real, kIlTable>(nb, grid, P, W, out, z64, direct, s);
-    if constexpr (sizeof(Real) == 8)
-        if (carlson) return adj_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, W, out, z64, direct, s);
+    if (carlson) return adj_wave_nb<1, double, Real, kIlCarlson>(nb, grid, P, W, out, z64, direct, s);
     return adj_wave_nb<1, double, Real, kIlExact>(nb, grid, P, W, out, z64, direct, s);
 }
 

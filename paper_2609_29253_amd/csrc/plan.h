@@ -42,16 +42,7 @@ inline double mean_shells(const TrDev* T, const int32_t* perm, int n, const KPar
 }
 
 // The share of the cylinders' pairs that the weighted areas serve (arc_fit), on the
-// same voxels and transducers.  With FP64 input and output, below 0.2
-// the kernels that evaluate every pair by Carlson's integral are faster, since
-// waves that hold both kinds of pair step through both (A + A^T on 48^3 voxels near
-// the axis x 64 cylinders, none served: 2.88 against 3.09 ms; 61 x 47 x 53 x 96,
-// 0.3 served: 8.34 against 8.09 ms; 96^3 x 32: 15.2 against 11.9 ms).  A launch of
-// few waves lasts as long as its slowest ones, which hold both kinds, so below 24576
-// every sampled pair has to be served (elements of a scan, A / A^T, Carlson against
-// mixed: 22 x 14 x 22 x 26, 3744 waves, 46 / 46 against 67 / 67 us; 28^3 x 64, 21952
-// waves, 195 / 215 against 210 / 243 us; 32^3 x 64, 32768 waves, 339 / 354 against
-// 324 / 337 us; 80^3 x 64 6.9 / 7.5 against 4.7 / 5.1 ms).
+// same voxels and transducers
 template <int NW>
 inline double arc_share(const TrDev* T, const int32_t* perm, int n, const KParams& P)
 {
@@ -75,6 +66,22 @@ inline double arc_share(const TrDev* T, const int32_t* perm, int n, const KParam
         }
     }
     return (double)fit / (64.0 * count);
+}
+
+// Whether a group of cylinders takes the kernels that evaluate every pair by Carlson's
+// integral: waves that hold both kinds of pair step through both.  Below a share of
+// 0.2 Carlson alone is faster (64 cylinders, A / A^T in ms, Carlson against mixed: FP32,
+// 32^3 voxels near the axis, none served, 0.91 / 0.99 against 1.00 / 1.10, 48^3 at 0.09 4.70 /
+// 5.05 against 4.98 / 5.45, 64^3 at 0.20 11.1 / 12.1 against 10.8 / 12.1, 0.39 6.48 / 7.19 against
+// 5.89 / 6.79; FP64, 48^3, none served, 3.21 / 3.53 against 3.29 / 3.60, 96^3 at 0.24 24.7 / 25.6
+// against 23.7 / 25.0).  A launch of few waves lasts as long as its slowest ones,
+// which hold both kinds, so there every sampled pair has to be served (elements of
+// a scan, us: FP32, 13824 waves, 0.93 served, 107 / 112 against 116 / 123, 21952 waves 171 / 191
+// against 159 / 188; FP64, 21952 waves, 0.79 served, 189 / 210 against 212 / 242, 32768 waves
+// 288 / 309 against 279 / 300).
+inline bool carlson_only(double share, int64_t waves, bool fp64)
+{
+    return share < (waves < (fp64 ? 24576 : 16384) ? 1.0 : 0.2);
 }
 
 // Transducers per work-group of the adjoint: as many work-groups as 4096 of a brick's

@@ -66,5 +66,7 @@ extern "C" double arc_share_of(const double* cyl, int nk, int n, double w, int f
     KParams P;
     std::memset(&P, 0, sizeof P);
     for (int a = 0; a < 3; ++a) P.n[a] = n;
-    return arc_share<2>(T.data(), perm.data(), nk, P);
+    return fp64 ? arc_share<2>(T.data(), perm.data(), nk, P) : arc_share<1>(T.data(), perm.data(), nk, P);
 }
+
+extern "C" int carlson_only_of(double share, long waves, int fp64) { return carlson_only(share, waves, fp64); }

@@ -83,3 +83,13 @@ def test_share_of_the_weighted_areas_from_a_bounded_sample(plan):
         assert K > 32 or len(seen) == len({0, 1, K // 3, K // 2, K - 2, K - 1})
     hidden = sum(share(plan, [wide if j == k else served for j in range(200)]) == 1.0 for k in range(200))
     assert hidden == 200 - 32
+
+
+@pytest.mark.parametrize("fp64,few", [(0, 16384), (1, 24576)])
+def test_groups_that_the_weight_does_not_serve_keep_one_kind_of_pair(plan, fp64, few):
+    fn = plan.carlson_only_of
+    fn.argtypes = [ctypes.c_double, ctypes.c_long, ctypes.c_int]
+    assert fn(0.0, 100, fp64) and fn(0.0, 10 ** 6, fp64) and fn(0.99, few - 1, fp64)
+    assert not fn(0.99, few, fp64) and not fn(1.0, 100, fp64) and not fn(0.25, 10 ** 6, fp64)
+    axis = [800.0, 0.12, 270.0, -3.0, -3.0, -3.0]      # voxels within 4 bins of the focal line
+    assert share(plan, [axis], n=12, w=0.5, fp64=fp64) == 0.0
