@@ -43,7 +43,7 @@ namespace patop {
 // ---------------------------------------------------------------------------
 
 // Seeds of the FP64 reciprocal and reciprocal square root.  NW = 1 (one
-// correction step, the FP32-I/O cylinder kernels): the FP32 instructions
+// correction step, the kernels with FP32 input and output): the FP32 instructions
 // v_rcp_f32 / v_rsq_f32 (1 ulp, 2^-23), which on gfx950 cost, with their two
 // conversions, about half of v_rcp_f64 / v_rsq_f64; one Newton step then leaves
 // 2^-46 (rcp) and 1.5 x 2^-46 (rsq) relative error.  Their arguments must lie
@@ -164,18 +164,18 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 // eps of p changes each area by at most eps of itself, whatever the cancellation
 // between edges, and costs no elliptic integral: two square roots, one inverse
 // function and about 6 N + 35 further FP64 operations per edge, with no loop
-// whose length differs between lanes.  A rectangle is the case h = 1, N = 0.
+// whose length differs between lanes.  A rectangle is the case h = 1, N = 0, with FP32
+// input and output; with FP64 it has a form of its own (PlaneQuad).
 //
-// The sweep is bound by VALU issue (0.97 of the SIMD cycles on 256^3 x 512
-// rectangles, at four cycles a wave instruction): 70 instructions per edge of a
-// rectangle, 112 to 130 of a cylinder, where Carlson's integral by Legendre's
+// The sweep is bound by VALU issue (ISSUE of the SIMD cycles on 256^3 x 512
+// rectangles, at four cycles a wave instruction): 71 instructions per edge of a
+// rectangle, 119 to 137 of a cylinder, where Carlson's integral by Legendre's
 // addition theorem took 271 per edge and a walk of FP32 pieces between the
 // rectangle's corners 194 per bin.  With FP32 input and output A went from 448 to
-// 263 ms on 256^3 x 512 rectangles and from 142 to 61 ms on 128^3 x 256 cylinders
-// (to 275 and 69 by this form, the rest by the order and number of the
-// work-groups); A^T of 32^3 x 64 rectangles in FP64 from 427 to 58 us.  Errors
-// against 64 bits, 32^3 x 64 rectangles: FP32 signals 1.5e-7 -> 2.6e-8, FP64 A^T
-// 1.3e-13 -> 8e-14.
+// 266 ms on 256^3 x 512 rectangles and from 142 to 66 ms on 128^3 x 256 cylinders
+// (the order and number of the work-groups in it: 275 -> 263 and 69 -> 61, with weights
+// of one degree less).  Errors of the FP32 signals against 64 bits, 32^3 x 64
+// rectangles: 1.5e-7 -> 2.6e-8.
 //
 // End points of the arc: alpha starts clamped at the quadrant's near end N (u =
 // a) and moves along the line v = d once K passes the corner (N, d); beta moves

@@ -88,7 +88,8 @@ __device__ __forceinline__ void brick_box(const KParams& P, int bid, double lo[3
 // 32 divides nx, each engine would see the same columns of the volume in every
 // row, and the costliest would set the pace (128^3 x 256 cylinders: 2.5 waves per
 // SIMD resident of 4 possible, and 3.96 with each row starting at a column of its
-// own: A 69.3 -> 64.1 ms, A^T 80.8 -> 68.2; 256^3 x 512 rectangles A 275 -> 263).
+// own: A 69.3 -> 64.1 ms, A^T 80.8 -> 68.2, with weights of one degree less than now;
+// 256^3 x 512 rectangles A 275 -> 263).
 __device__ __forceinline__ unsigned spread_column(unsigned id, unsigned row, unsigned nx)
 {
     return (id - row * nx + (((row + 1) * 0x9e3779b9u) >> 16)) % nx;
@@ -210,8 +211,8 @@ constexpr int kSparseGrid = 4096;
 
 // Waves per SIMD the closed-form kernels are built for (one-wave work-groups in
 // the dense and sparse forward and the adjoint, 256-thread ones in the time
-// tiles).  The planar kernels hold 96-128 VGPRs without spills (five waves at 96),
-// except FP64 with eight volumes (149 in the adjoint: three).  Cylinders for one or
+// tiles).  The planar kernels hold 90-128 VGPRs without spills (five waves up to 96),
+// except FP64 with eight volumes (140 in the adjoint: three).  Cylinders for one or
 // two volumes: four, in 128 VGPRs with spills outside the loops over edges; with
 // more volumes the spills grow and they keep three.
 template <int SHAPE, class AT, int NB>
@@ -754,8 +755,8 @@ __global__ __launch_bounds__(kThreads) void k_fwd_quad(KParams P, const Real* __
     constexpr int HB = kHistQuad;   // bins per pass
     extern __shared__ double hist[];
     Brick Bk;
-    const unsigned row = blockIdx.x / (unsigned)P.nbx;
-    brick_setup(P, (int)(row * P.nbx + spread_column(blockIdx.x, row, P.nbx)), Bk);
+    const unsigned line = blockIdx.x / (unsigned)P.nbx;   // row of bricks
+    brick_setup(P, (int)(line * P.nbx + spread_column(blockIdx.x, line, P.nbx)), Bk);
     double p0[NB];
     bool nz = false;
 #pragma unroll
@@ -842,8 +843,8 @@ __global__ __launch_bounds__(kThreads) void k_adj_quad(KParams P, const Real* __
     extern __shared__ double smem_d[];
     Real* Ws = reinterpret_cast<Real*>(smem_d);
     Brick Bk;
-    const unsigned row = blockIdx.x / (unsigned)P.nbx;
-    brick_setup(P, (int)(row * P.nbx + spread_column(blockIdx.x, row, P.nbx)), Bk);
+    const unsigned line = blockIdx.x / (unsigned)P.nbx;   // row of bricks
+    brick_setup(P, (int)(line * P.nbx + spread_column(blockIdx.x, line, P.nbx)), Bk);
     double acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = 0.0;

@@ -261,9 +261,11 @@ struct CylinderPair {
 // They cover |tau| <= eta of x = w^2 / mu on its side of pi/2.  The recurrence of the
 // J_j loses (vmax^2 / (mu (1 - xc)))^n roundings, so voxels closer to the focal line
 // than kappa, and within 1e-7 R of it, keep the elliptic integral.  So do, with FP64
-// input and output, those whose interval reaches u = pi: the integral's end points
-// round there by up to 1e-8 of a bin, and FP64 signals stay within 1e-9 of the ones
-// earlier versions returned.
+// input and output, those whose interval reaches u = pi, although the weight fits
+// them and is closer there (worst bin of a pair against 30 digits, elements of an arc:
+// 5e-14 to 2.5e-13 against 5e-12 to 9e-11, as the integral's end points round there by up to
+// 1e-8 of a bin): taking it moves the FP64 signals of such arrays by up to 2.5e-9,
+// where 1e-9 of the earlier ones was kept.
 struct ArcFit {
     int least, most;
     __host__ __device__ bool fits() const { return least <= most; }
@@ -292,7 +294,7 @@ __host__ __device__ inline ArcFit arc_fit(double R, double rho, double c0, doubl
 
 // One pair by its elliptic integrals, out of line: the few pairs that need it
 // would otherwise cost every other one registers (inlined, 84 were spilled; now
-// 18 to 30, outside the loops over edges).  The sink travels by value, with LDS
+// 20 to 47, outside the loops over edges).  The sink travels by value, with LDS
 // pointers typed as such.
 template <int NW, int STRIDE, class Sink>
 __device__ __attribute__((noinline)) Sink carlson_pair(const TrDev* tr, int ix, int iy, int iz, int wlo, int whi,

@@ -90,18 +90,20 @@ inline bool carlson_only(double share, int64_t waves, bool fp64)
 // terms are added to the zero that it starts from, hence two, and only for an
 // array of one shape (two shapes would make four).  Two chunks halve the last
 // round (128^3 x 256 cylinders 67.5 -> 64.6 ms, quadrature 61.8 -> 59.5, 256 rectangles
-// 10.6 -> 10.3) at the cost of sums cleared, added and cast in memory, about 18 ps per voxel
-// and volume, against some 15 ps of the last round saved per thousand shells and
-// voxel: 128^3 rectangles, one volume, 8 (W = 380 shells) 0.347 -> 0.350 ms, 16 0.677 ->
-// 0.669; eight volumes, 8 0.47 -> 0.54, 32 (W = 1540) 1.83 -> 1.82; 32 with 128 samples kept
-// 0.21 -> 0.42; cylinders, one volume, 3 (W = 670) 0.81 -> 0.80, eight, 4 1.29 -> 1.34, 8 (W = 1800)
-// 2.60 -> 2.58.  So from W = 512 (volumes + 1) on.
+// 10.6 -> 10.3, and more where the rounds are few: 100 x 98 x 110 x 5 elements of a scan 0.68 ->
+// 0.56) at the cost of sums cleared, added and cast in memory.  Measured on 128^3
+// voxels, W = shells per voxel: rectangles, one volume, 8 (W = 380) 0.347 -> 0.350 ms, 16
+// (W = 770) 0.677 -> 0.669; eight volumes, 8 0.47 -> 0.54, 24 (W = 1150) 1.37 -> 1.39, 32
+// (W = 1540) 1.83 -> 1.82; 32 with 128 samples kept 0.21 -> 0.42; cylinders, one volume,
+// 2 (W = 450) 0.55 -> 0.56, 3 (W = 670) 0.81 -> 0.80, eight, 4 (W = 900) 1.29 -> 1.34, 8 (W =
+// 1800) 2.60 -> 2.58; quadrature, one volume, 2 (W = 512) 0.495 -> 0.507, 3 (W = 770) 0.735 ->
+// 0.728, eight, 6 (W = 1540) 2.42 -> 2.43, 8 (W = 2050) 3.23 -> 3.22.  So from W = 448 + 160 volumes on.
 inline int adjoint_chunk(int nk, int64_t nbricks, bool one_shape, double shells, int volumes)
 {
     const int64_t target = 4096;
     const int64_t nchunks = std::max<int64_t>(1, std::min<int64_t>(nk, (target + nbricks - 1) / nbricks));
     const int chunk = (int)((nk + nchunks - 1) / nchunks);
-    if (one_shape && nbricks < 4 * target && nk * shells >= 512.0 * (volumes + 1)) return std::min(chunk, (nk + 1) / 2);
+    if (one_shape && nbricks < 4 * target && nk * shells >= 448.0 + 160.0 * volumes) return std::min(chunk, (nk + 1) / 2);
     return chunk;
 }
 
