@@ -169,12 +169,12 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 //
 // The sweep is bound by VALU issue (ISSUE of the SIMD cycles on 256^3 x 512
 // rectangles, at four cycles a wave instruction): 71 instructions per edge of a
-// rectangle, 119 to 137 of a cylinder, where Carlson's integral by Legendre's
+// rectangle, 113 to 137 of a cylinder, where Carlson's integral by Legendre's
 // addition theorem took 271 per edge and a walk of FP32 pieces between the
 // rectangle's corners 194 per bin.  With FP32 input and output A went from 448 to
-// 266 ms on 256^3 x 512 rectangles and from 142 to 66 ms on 128^3 x 256 cylinders
+// 265 ms on 256^3 x 512 rectangles and from 142 to 65 ms on 128^3 x 256 cylinders
 // (the order and number of the work-groups in it: 275 -> 263 and 69 -> 61, with weights
-// of one degree less).  Errors of the FP32 signals against 64 bits, 32^3 x 64
+// of a lower degree).  Errors of the FP32 signals against 64 bits, 32^3 x 64
 // rectangles: 1.5e-7 -> 2.6e-8.
 //
 // End points of the arc: alpha starts clamped at the quadrant's near end N (u =
@@ -183,31 +183,41 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 
 // h's factor (1 - x)^(-1/2) = (1 - xc)^(-1/2) (1 - tau)^(-1/2), tau = (x - xc) /
 // (1 - xc): interpolants of degree n at Chebyshev nodes on |tau| <= eta, by level.
-// Relative error with FP32 input and output 2.2e-11, 2.3e-11 and 5.7e-11, three orders
-// below the output's rounding and no more than Carlson's integral leaves there (worst
-// bin of a pair over its largest, median / 95 % / worst, Carlson and this: elements
+// Relative error with FP32 input and output 1.9e-11, 2.2e-11, 2.3e-11 and 5.7e-11, three
+// orders below the output's rounding: about what Carlson's integral leaves in the median,
+// less in the worst (worst bin of a pair over its largest, median / 95 % / worst, Carlson and this: elements
 // of a scan at U = 1 1.7e-11 / 2.4e-10 / 2.3e-9 and 2.0e-11 / 7e-11 / 1.1e-10, at U = 11 2.1e-10 /
-// 1.9e-9 / 2e-8 and 3.3e-11 / 5e-10 / 1e-9, of an arc 5e-8 / 1.4e-7 / 1.7e-7 and 1.2e-11 /
-// 1.7e-11 / 2e-11); with FP64 6.2e-14, 1.0e-13 and 3.3e-13.  Degrees 4, 5, 7 (1.6e-9 at
-// U = 1, whatever the element) take 62.1 and 64.6 ms on 128^3 x 256 cylinders where
-// these take 66.1 and 69.0, 67.6 on the scan of 200^3 x 64 where these take 72.8.  kappa
-// bounds vmax^2 / (mu (1 - xc)), whose n-th power multiplies the roundings of the J_j.
+// 1.9e-9 / 2e-8 and 3.3e-11 / 5e-10 / 1e-9, of an arc 5e-8 / 1.4e-7 / 1.7e-7 and 1.1e-11 /
+// 1.8e-11 / 2e-11); with FP64 6.2e-14, 1.0e-13 and 3.3e-13.  A / A^T of 128^3 x 256 cylinders,
+// A^T of the scan of 200^3 x 64 in ms: 64.6 / 67.8, 73.1; without the first level 66.1 /
+// 69.0, 72.8; degrees 4, 5, 7 on 0.04, 0.08, 0.16, which leave 1.6e-9 whatever the element,
+// 62.1 / 64.6, 67.6.  kappa bounds vmax^2 / (mu (1 - xc)), whose n-th power multiplies the
+// roundings of the J_j.
 template <int NW, int LEVEL> struct Weight;
+// (levels, the lowest degree first)
+template <int NW> struct Levels { static constexpr int n = 3; };
+template <> struct Levels<1> { static constexpr int n = 4; };
 template <> struct Weight<1, 0> {
+    static constexpr int n = 4;
+    static constexpr double eta = 0.0165, kappa = 3.2;
+    static constexpr double c[n + 1] = {
+        1.0, 0.49999999429819714, 0.374999994773313, 0.31258376819134176, 0.27351428791320237};
+};
+template <> struct Weight<1, 1> {
     static constexpr int n = 5;
     static constexpr double eta = 0.038, kappa = 2.6;
     static constexpr double c[n + 1] = {
         1.0000000000212659, 0.5000000000197475, 0.3749997349316204, 0.31249975385743234, 0.27392681105161915,
         0.24654812125416245};
 };
-template <> struct Weight<1, 1> {
+template <> struct Weight<1, 2> {
     static constexpr int n = 7;
     static constexpr double eta = 0.104, kappa = 2.0;
     static constexpr double c[n + 1] = {
         0.9999999999785899, 0.4999999999797752, 0.37500006332410346, 0.3125000598183644, 0.27340827460690964,
         0.24606614306016883, 0.22989139768446637, 0.2135395082670361};
 };
-template <> struct Weight<1, 2> {
+template <> struct Weight<1, 3> {
     static constexpr int n = 8;
     static constexpr double eta = 0.16, kappa = 1.8;
     static constexpr double c[n + 1] = {

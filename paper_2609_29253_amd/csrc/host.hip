@@ -370,7 +370,7 @@ pat_status pat_set_geometry(pat_ctx* c, const pat_transducer* tr, int32_t K, con
     // Work-groups of a brick's size that a launch is split into at least, by chunks
     // of transducers.  The forward adds into f with atomics whatever its chunks, and
     // eight times as many as the adjoint's (adjoint_chunk) shorten its last round (128^3
-    // x 256 cylinders, with weights of one degree less than now, 62.4 ms with four times,
+    // x 256 cylinders, with weights of a lower degree than now, 62.4 ms with four times,
     // 61.2 with eight, 61.0 with sixteen; quadrature on 64^3 x 64 2.83 ms with one, 2.56
     // with four or eight, on 128^3 x 64 24.9, 24.3 and 24.0).
     const int target_fwd = 32768;

@@ -88,7 +88,7 @@ __device__ __forceinline__ void brick_box(const KParams& P, int bid, double lo[3
 // 32 divides nx, each engine would see the same columns of the volume in every
 // row, and the costliest would set the pace (128^3 x 256 cylinders: 2.5 waves per
 // SIMD resident of 4 possible, and 3.96 with each row starting at a column of its
-// own: A 69.3 -> 64.1 ms, A^T 80.8 -> 68.2, with weights of one degree less than now;
+// own: A 69.3 -> 64.1 ms, A^T 80.8 -> 68.2, with weights of a lower degree than now;
 // 256^3 x 512 rectangles A 275 -> 263).
 __device__ __forceinline__ unsigned spread_column(unsigned id, unsigned row, unsigned nx)
 {

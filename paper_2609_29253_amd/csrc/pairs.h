@@ -274,18 +274,18 @@ template <int NW>
 __host__ __device__ inline ArcFit arc_fit(double R, double rho, double c0, double c1, double cm, double cp, bool ok0,
                                           bool ok1, double vmax, bool inpi)
 {
-    using W0 = Weight<NW, 0>;
-    using W1 = Weight<NW, 1>;
-    using W2 = Weight<NW, 2>;
+    constexpr int top = Levels<NW>::n - 1;
     const double mu = 4.0 * R * rho, v2 = vmax * vmax;
-    ArcFit r{0, mu >= 4e-7 * R * R && !(NW >= 2 && inpi) ? 2 : -1};
+    ArcFit r{0, mu >= 4e-7 * R * R && !(NW >= 2 && inpi) ? top : -1};
     for (int i = 0; i < 2; ++i) {
         if (!(i ? ok1 : ok0)) continue;
         const double ca = i ? cm : c0, cb = i ? cp : c1, g = ca + cb > 0.0 ? 0.5 : -0.5;
         const double xa = fma(-g, ca, 0.5), xb = fma(-g, cb, 0.5);
         const double one = 1.0 - 0.5 * (xa + xb), del = 0.5 * fabs(xb - xa), m1 = mu * one;
-        const int least = del <= W0::eta * one ? 0 : del <= W1::eta * one ? 1 : del <= W2::eta * one ? 2 : 3;
-        const int most = v2 <= W2::kappa * m1 ? 2 : v2 <= W1::kappa * m1 ? 1 : v2 <= W0::kappa * m1 ? 0 : -1;
+        const int least = (del > Weight<NW, 0>::eta * one) + (del > Weight<NW, 1>::eta * one) +
+                          (top > 2 && del > Weight<NW, top - 1>::eta * one) + (del > Weight<NW, top>::eta * one);
+        const int most = (v2 <= Weight<NW, 0>::kappa * m1) + (v2 <= Weight<NW, 1>::kappa * m1) +
+                         (top > 2 && v2 <= Weight<NW, top - 1>::kappa * m1) + (v2 <= Weight<NW, top>::kappa * m1) - 1;
         r.least = r.least > least ? r.least : least;
         r.most = r.most < most ? r.most : most;
     }
@@ -322,8 +322,8 @@ struct ArcCylinderPair {
     const double* tab;
     int list, nq;            // non-empty quadrants (2 bits each, in sweep order) and their number
     int bits;                // bit 0 / 1: U / V interval 0 has weight 2; bit 2 / 3: U interval 0 ends at
-                             // u = 0 / pi; bits 4 / 5: the weight's level is at least 1 / 2; bits 6-8:
-                             // level 0 / 1 / 2 does not serve, all of them for Carlson's path
+                             // u = 0 / pi; bits 4-5: the weight's least level; bits 6-8: the number of
+                             // levels that serve from the lowest on, 0 for Carlson's path
     int level;               // the pair's own, the wave's after agree()
     const TrDev* tr;         // the pair, for Carlson's path
     int ix, iy, iz;
@@ -363,10 +363,7 @@ struct ArcCylinderPair {
         bits = (in0 || inpi ? 1 : 0) | (V.n == 2 ? 2 : 0) | (in0 ? 4 : 0) | (inpi ? 8 : 0);
         const ArcFit fit = arc_fit<NW>(R, rho, c0, c1, cm, cp, uok[0], uok[1], vmax, inpi);
         level = 0;
-        if (!fit.fits()) {
-            bits |= 7 << 6;
-            return;
-        }
+        if (!fit.fits()) return;
         level = fit.least;
         // the non-empty quadrants in decreasing order of their number of bins
         // (nearest to farthest corner, estimated in FP32): the wave steps
@@ -397,7 +394,7 @@ struct ArcCylinderPair {
                 rank += (qj != qi) && (len[qj] > len[qi] || (len[qj] == len[qi] && qj < qi));
             if (ok[qi]) { list |= qi << (2 * rank); ++nq; }
         }
-        bits |= (fit.least << 4) | ((6 << fit.most) & 6) << 6;
+        bits |= (fit.least << 4) | (fit.most + 1) << 6;
         box[0 * STRIDE] = cm; box[1 * STRIDE] = fabs(sm);
         box[2 * STRIDE] = cp; box[3 * STRIDE] = fabs(sp);
         box[4 * STRIDE] = V.lo[0]; box[5 * STRIDE] = V.hi[0]; box[6 * STRIDE] = V.hi[1];
@@ -411,7 +408,8 @@ struct ArcCylinderPair {
     // the weight's error.
     __device__ __forceinline__ void agree(bool valid)
     {
-        level = __any(valid && (bits & 32)) ? 2 : __any(valid && (bits & 16)) ? 1 : 0;
+        const int own = valid ? (bits >> 4) & 3 : 0;
+        level = __any(own > 2) ? 3 : __any(own > 1) ? 2 : __any(own > 0) ? 1 : 0;
     }
     // p(om) = scale (1 - x)^(-1/2): Weight's polynomial in tau = al om + be, expanded
     template <class Wt>
@@ -476,7 +474,7 @@ struct ArcCylinderPair {
     template <int LEVEL, class Sink>
     __device__ __forceinline__ void arcs_or_carlson(int wlo, int whi, Sink& sink, double r0)
     {
-        if (bits & (64 << LEVEL))
+        if ((bits >> 6) <= LEVEL)
             sink.take(carlson_pair<NW, STRIDE>(tr, ix, iy, iz, wlo, whi, r0, (LdsDouble*)box, sink.give()));
         else
             arcs<Weight<NW, LEVEL>>(wlo, whi, sink, r0);
@@ -484,7 +482,9 @@ struct ArcCylinderPair {
     template <class Sink>
     __device__ __forceinline__ void sweep(int wlo, int whi, Sink& sink, double r0)
     {
-        if (level == 2)
+        if (Levels<NW>::n > 3 && level == 3)
+            arcs_or_carlson<Levels<NW>::n - 1>(wlo, whi, sink, r0);
+        else if (level == 2)
             arcs_or_carlson<2>(wlo, whi, sink, r0);
         else if (level == 1)
             arcs_or_carlson<1>(wlo, whi, sink, r0);
