@@ -167,8 +167,8 @@ __device__ __forceinline__ float sqrt_t(float x) { return __builtin_amdgcn_sqrtf
 // whose length differs between lanes.  A rectangle is the case h = 1, N = 0, with FP32
 // input and output; with FP64 it has a form of its own (PlaneQuad).
 //
-// The sweep is bound by VALU issue (ISSUE of the SIMD cycles on 256^3 x 512
-// rectangles, at four cycles a wave instruction): 71 instructions per edge of a
+// The sweep is bound by VALU issue (1.02 of the SIMD cycles on 256^3 x 512
+// rectangles, at four cycles a wave instruction; FP32 ones issue faster): 71 instructions per edge of a
 // rectangle, 113 to 137 of a cylinder, where Carlson's integral by Legendre's
 // addition theorem took 271 per edge and a walk of FP32 pieces between the
 // rectangle's corners 194 per bin.  With FP32 input and output A went from 448 to
